@@ -19,9 +19,10 @@
 // exact products in FP32.  One 32x32x16 step covers exactly one 16-element
 // NVFP4 block per row.  g_a * g_b is applied in the epilogue.
 //
-// Tiling: 128 x 128 output tile per 256-thread workgroup, 2 x 2 waves of
-// 64 x 64 (2 x 2 MFMA tiles of 32 x 32), K staged 128 elements at a time
-// through LDS.
+// This file holds the choice of kernel for a product and the general kernel,
+// which runs what the tiled ones do not take: K == 0 (it writes zeros) and, with
+// M > 64, rows of more than kKsplitMaxK elements.  Tiling: 128 x 128 output tile per 256-thread workgroup, 2 x 2 waves of 64 x 64 (2 x 2
+// MFMA tiles of 32 x 32), K staged 128 elements at a time through LDS.
 #include "fp4_device.h"
 #include "internal.h"
 
@@ -192,17 +193,69 @@ __global__ __launch_bounds__(kThreads) void gemm_w4a4_kernel(
 
 }  // namespace
 
+namespace {
+
+// Which kernel runs a product of M > 64 rows: the one with the least estimated
+// time, c + rounds (e + t K) with rounds = tiles / 256 CUs, rounded up, and a
+// time per K that one round alone does not fall below (too few waves per CU
+// to keep the matrix cores or the loads busy).  The numbers (nanoseconds; t per
+// element of K) are a fit to measurements over M = 65 .. 2048 and (N, K) =
+// (4608, 3584), (3584, 18944), (37888, 3584), (17920, 1536), (5120, 1280),
+// (1792, 5120), (5120, 3456), (7168, 5120), one HIP graph, weights from HBM.
+// Where it picks another kernel than the fastest, the two lay within 12% of
+// each other.  For example, in us, for 64 x 64 / 64 x 128 / 128 x 128 / 256 x 256:
+//   NVFP4  256 x 3584 x 18944: 45 / 85 / 131 / 331     1024 x 37888 x 3584: 386 / 277 / 259 / 237
+//   MXFP4  128 x 4608 x 3584: 8.2 / 12.7 / 15.4 / 28   777 x 7168 x 5120: 46 / 41 / 29 / 40
+//          2048 x 4608 x 3584: 55 / 38 / 35 / 29
+// The rule uses sizes alone, so a shape always runs the same kernel.
+struct TileCost {
+    int tm, tn;
+    double c, e, t, alone;
+};
+constexpr TileCost kCost[2][4] = {
+    // NVFP4: 64 x 64, 64 x 128, 128 x 128, 256 x 256
+    {{64, 64, 3000, 1800, 2.15, 0}, {64, 128, 4000, 0, 3.6, 4.2}, {128, 128, 4000, 0, 6.9, 7.6}, {256, 256, 4000, 0, 22, 20}},
+    // MXFP4
+    {{64, 64, 3000, 1200, 1.3, 0}, {64, 128, 3000, 700, 2.0, 3.4}, {128, 128, 3000, 700, 2.9, 4.0}, {256, 256, 3000, 700, 7.7, 0}},
+};
+
+// 0 .. 2: KsplitTile; 3: 256 x 256 tiles
+int pick_tile(Fmt fmt, int64_t M, int64_t N, int64_t K, bool big_ok) {
+    int best = 0;
+    double least = 0;
+    for (int i = 0; i < (big_ok ? 4 : 3); ++i) {
+        const TileCost &q = kCost[fmt == kMX][i];
+        const int64_t tiles = ((M + q.tm - 1) / q.tm) * ((N + q.tn - 1) / q.tn);
+        const double rounds = (double)((tiles + 255) / 256);
+        const double t = rounds == 1 && q.alone > 0 ? q.alone : q.t;
+        const double est = q.c + rounds * (q.e + t * (double)K);
+        if (i == 0 || est < least) {
+            best = i;
+            least = est;
+        }
+    }
+    return best;
+}
+
+}  // namespace
+
 hipError_t launch_gemm(Fmt fmt, int64_t M, int64_t N, int64_t K, const uint8_t *a_codes,
                        const uint8_t *a_scales, const float *ga, const uint8_t *b_codes,
                        const uint8_t *b_scales, const float *gb, void *y, bool y_bf16, int64_t ldy,
                        hipStream_t stream) {
     if (M == 0 || N == 0) return hipSuccess;
-    if (M > 64 && gemm_tile256_supported(fmt, M, N, K, ldy))
-        return launch_gemm_tile256(fmt, M, N, K, a_codes, a_scales, ga, b_codes, b_scales, gb, y,
-                                   y_bf16, ldy, stream);
     if (M <= 64 && K > 0)
         return launch_gemm_skinny(fmt, M, N, K, a_codes, a_scales, ga, b_codes, b_scales, gb, y, y_bf16,
                                   ldy, false, stream);
+    if (K > 0 && K <= kKsplitMaxK) {
+        const int tile = pick_tile(fmt, M, N, K, gemm_tile256_supported(fmt, M, N, K, ldy));
+        if (tile == 3)
+            return launch_gemm_tile256(fmt, M, N, K, a_codes, a_scales, ga, b_codes, b_scales, gb, y,
+                                       y_bf16, ldy, stream);
+        return launch_gemm_ksplit((KsplitTile)tile, fmt, M, N, K, a_codes, a_scales, ga, b_codes, b_scales, gb, y,
+                                  y_bf16, ldy, stream);
+    }
+    // K == 0 (writes zeros), or rows beyond the 32-bit offsets of the tiled kernels
     dim3 grid((unsigned)((N + BN - 1) / BN), (unsigned)((M + BM - 1) / BM)), block(kThreads);
     if (fmt == kMX)
         hipLaunchKernelGGL(gemm_w4a4_kernel<kMX>, grid, block, 0, stream, M, N, K, a_codes, a_scales,

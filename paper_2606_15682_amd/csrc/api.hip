@@ -383,7 +383,7 @@ reqat_status run_linear(reqat_format fmt, int64_t M, int64_t N, int64_t K, const
                                 workspace, nseg <= kMaxSegments ? table : nullptr, nseg, stream, kCodes);
     if (st != REQAT_OK) return st;
     hipError_t e = packed && K > 0
-                       ? launch_gemm_skinny(nv ? kNV : kMX, M, N, K, a_codes, a_scales, x_tensor_scale, w_codes,
+                       ? launch_gemm_decode(nv ? kNV : kMX, M, N, K, a_codes, a_scales, x_tensor_scale, w_codes,
                                             w_scales, w_tensor_scale, y, y_dtype == REQAT_DT_BF16, ldy, true,
                                             reinterpret_cast<hipStream_t>(stream))
                        : launch_gemm(nv ? kNV : kMX, M, N, K, a_codes, a_scales, x_tensor_scale, w_codes,
@@ -461,7 +461,7 @@ reqat_status reqat_gemm_w4a4_packed(reqat_format fmt, int64_t M, int64_t N, int6
         return REQAT_E_ALIGN;
     const hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     // K == 0: the generic product writes zeros and reads no operand
-    hipError_t e = K > 0 ? launch_gemm_skinny(nv ? kNV : kMX, M, N, K, a_codes, a_scales, a_tensor_scale,
+    hipError_t e = K > 0 ? launch_gemm_decode(nv ? kNV : kMX, M, N, K, a_codes, a_scales, a_tensor_scale,
                                               reinterpret_cast<const uint8_t *>(packed),
                                               packed_scales(packed, N, K), b_tensor_scale, y,
                                               y_dtype == REQAT_DT_BF16, ldy, true, st)

@@ -242,7 +242,62 @@ int pick_tile(Fmt fmt, int64_t M, int64_t N, int64_t K, bool big_ok) {
     return best;
 }
 
+// 17 to 64 rows: the skinny kernel (16 rows of W per workgroup, which reads all of
+// X from L2 in 16-byte pieces: rounds of 256 workgroups, a time per K that grows
+// with the tiles of 16 rows of X), or a tile that takes X through LDS once for 32 to
+// 128 rows of W.  Up to 16 rows the skinny kernel is the faster one nearly
+// everywhere.  Same form of estimate, fitted over the same weights from HBM and
+// M = 17, 32, 48, 64.  For example, in us, skinny / the pick:
+//   MXFP4  64 x 27648 x 5120: 67 / 25    64 x 5120 x 13824: 39 / 19    64 x 2048 x 1536: 4.8 / 4.8 (skinny; 64 x 32: 6.0)
+//   NVFP4  64 x 27648 x 5120: 79 / 33    32 x 7168 x 5120: 12.1 / 10   64 x 1792 x 5120: 12.1 / 12.1 (skinny; 64 x 32: 13)
+struct DecodeCost {
+    int tm, tn;                                 // tn = 16: the skinny kernel
+    double c, t;
+};
+constexpr DecodeCost kDecode[2][7] = {
+    // NVFP4: skinny of two, three, four row tiles; 32 x 32, 32 x 128; 64 x 32, 64 x 64
+    {{32, 16, 2800, 0.93}, {48, 16, 2800, 1.3}, {64, 16, 2800, 1.8},
+     {32, 32, 4200, 1.15}, {32, 128, 4500, 3.8}, {64, 32, 4000, 1.5}, {64, 64, 4000, 2.7}},
+    // MXFP4
+    {{32, 16, 2000, 0.85}, {48, 16, 2400, 1.17}, {64, 16, 3000, 1.4},
+     {32, 32, 3000, 1.0}, {32, 128, 3800, 2.4}, {64, 32, 3200, 1.15}, {64, 64, 3500, 1.8}},
+};
+
+// -1: the skinny kernel; else the KsplitTile.  Sizes alone, so that packed and
+// row-major weights of a shape give the same result.
+int pick_decode(Fmt fmt, int64_t M, int64_t N, int64_t K) {
+    if (M <= 16 || K > kKsplitMaxK) return -1;
+    constexpr int kTile[7] = {-1, -1, -1, kTile32x32, kTile32x128, kTile64x32, kTile64x64Few};
+    int best = -1;
+    double least = 0;
+    bool skinny = true;                         // the first skinny entry that holds M counts
+    for (int i = 0; i < 7; ++i) {
+        const DecodeCost &q = kDecode[fmt == kMX][i];
+        if (q.tn == 16 ? !skinny || M > q.tm : q.tm != (M <= 32 ? 32 : 64)) continue;
+        if (q.tn == 16) skinny = false;
+        const int64_t tiles = (N + q.tn - 1) / q.tn;
+        const double est = q.c + (double)((tiles + 255) / 256) * q.t * (double)K;
+        if (q.tn == 16 || est < least) {
+            best = kTile[i];
+            least = est;
+        }
+    }
+    return best;
+}
+
 }  // namespace
+
+hipError_t launch_gemm_decode(Fmt fmt, int64_t M, int64_t N, int64_t K, const uint8_t *a_codes,
+                              const uint8_t *a_scales, const float *ga, const uint8_t *b_codes,
+                              const uint8_t *b_scales, const float *gb, void *y, bool y_bf16, int64_t ldy,
+                              bool packed, hipStream_t stream) {
+    const int tile = pick_decode(fmt, M, N, K);
+    if (tile < 0)
+        return launch_gemm_skinny(fmt, M, N, K, a_codes, a_scales, ga, b_codes, b_scales, gb, y, y_bf16, ldy, packed,
+                                  stream);
+    return launch_gemm_ksplit((KsplitTile)tile, fmt, M, N, K, a_codes, a_scales, ga, b_codes, b_scales, gb, y, y_bf16,
+                              ldy, packed, stream);
+}
 
 hipError_t launch_gemm(Fmt fmt, int64_t M, int64_t N, int64_t K, const uint8_t *a_codes,
                        const uint8_t *a_scales, const float *ga, const uint8_t *b_codes,
@@ -250,7 +305,7 @@ hipError_t launch_gemm(Fmt fmt, int64_t M, int64_t N, int64_t K, const uint8_t *
                        hipStream_t stream) {
     if (M == 0 || N == 0) return hipSuccess;
     if (M <= 64 && K > 0)
-        return launch_gemm_skinny(fmt, M, N, K, a_codes, a_scales, ga, b_codes, b_scales, gb, y, y_bf16,
+        return launch_gemm_decode(fmt, M, N, K, a_codes, a_scales, ga, b_codes, b_scales, gb, y, y_bf16,
                                   ldy, false, stream);
     if (K > 0 && K <= kKsplitMaxK) {
         const int tile = pick_tile(fmt, M, N, K, gemm_tile256_supported(fmt, M, N, K, ldy));
@@ -258,7 +313,7 @@ hipError_t launch_gemm(Fmt fmt, int64_t M, int64_t N, int64_t K, const uint8_t *
             return launch_gemm_tile256(fmt, M, N, K, a_codes, a_scales, ga, b_codes, b_scales, gb, y,
                                        y_bf16, ldy, stream);
         return launch_gemm_ksplit((KsplitTile)tile, fmt, M, N, K, a_codes, a_scales, ga, b_codes, b_scales, gb, y,
-                                  y_bf16, ldy, stream);
+                                  y_bf16, ldy, false, stream);
     }
     // K == 0 (writes zeros), or rows beyond the 32-bit offsets of the tiled kernels
     dim3 grid((unsigned)((N + BN - 1) / BN), (unsigned)((M + BM - 1) / BM)), block(kThreads);

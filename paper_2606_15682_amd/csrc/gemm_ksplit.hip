@@ -19,6 +19,10 @@
 // other (loads, then reads, then MFMAs) a stage of 34 KB took 1.03 us on
 // MXFP4 instead of 0.45.
 //
+// 17 to 64 rows take tiles of 32 or 64 rows of X, from row-major weights or from
+// the packed decode image (gemm_skinny.hip), which lies in LDS as it lies in
+// memory; the operands are the same, and so is the result, bit for bit.
+//
 // What bounds each tile: NVFP4 the matrix cores and the decode beside them
 // (64 x 64: 2.1 us per 1000 elements of K with one tile per CU, 0.93 us would be
 // the MFMAs alone), MXFP4 the load path (64 x 64: 1.3 us; 128 x 128: 4 us, 5 for two
@@ -36,6 +40,7 @@
 #include <type_traits>
 
 #include "fp4_device.h"
+#include "g2l.h"
 #include "internal.h"
 
 namespace reqat {
@@ -49,27 +54,6 @@ typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 typedef __bf16 v4bf __attribute__((ext_vector_type(4)));
 
-// Direct-to-LDS loads: lane i's 16 (4) bytes land at LDS address l + 16 i (4 i).
-// Inline asm, so that the compiler does not wait for all of them before every
-// LDS read; the kernel orders them itself.
-__device__ __forceinline__ void g2l16(const uint8_t *base, uint32_t voff, uint8_t *l) {
-    asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "{m0}"((uint32_t)(uintptr_t)l));
-}
-__device__ __forceinline__ void g2l4(const uint8_t *base, uint32_t voff, uint8_t *l) {
-    asm volatile("global_load_lds_dword %0, %1" ::"v"(voff), "s"(base), "{m0}"((uint32_t)(uintptr_t)l));
-}
-
-// All but the wave's N newest loads have landed and its LDS reads are done; then
-// the workgroup's barrier.  The LDS wait is the builtin, so that the compiler
-// knows it: it would otherwise wait for the reads of the next stage before the
-// first MFMA on operands that were read long ago.
-template <int N> __device__ __forceinline__ void wait_and_meet() {
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-    __builtin_amdgcn_s_waitcnt(0xC07F);                     // lgkmcnt(0), the other counters at their maximum
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
-
 __device__ __forceinline__ uint32_t pick(const uint4 &q, int s) {
     return s == 0 ? q.x : s == 1 ? q.y : s == 2 ? q.z : q.w;
 }
@@ -81,14 +65,6 @@ __device__ __forceinline__ v8h decode8(uint32_t c, v2h s) {
     const v2h p2 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(c, 1.0f, 2) * s;
     const v2h p3 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(c, 1.0f, 3) * s;
     return v8h{p0[0], p0[1], p1[0], p1[1], p2[0], p2[1], p3[0], p3[1]};
-}
-
-// Calls f(integral_constant<int, J>) for J = B .. E-1, unrolled at compile time.
-template <int B, int E, typename F> __device__ __forceinline__ void static_for(F &&f) {
-    if constexpr (B < E) {
-        f(std::integral_constant<int, B>{});
-        static_for<B + 1, E>(f);
-    }
 }
 
 // RM x RN MFMA tiles of 32 x 32 per wave; WM x WN waves cover the workgroup's
@@ -116,6 +92,9 @@ struct Cfg {
     static constexpr int SPP = ROWS / SRPI / GS;            // scale loads per stage, and per wave and stage
     static constexpr int SL = (SPP + WAVES - 1) / WAVES;    // (where they do not split evenly, the last one is repeated)
     static constexpr int LPS = CL + SL;
+    // packed weights (units of 16 rows x 256 elements, see gemm_skinny.hip): units per row
+    // group and stage, a unit's scale bytes, a row group's scale bytes per scale group
+    static constexpr int CPS = KS / 256, SU = 16 * 256 / B, RUN = 16 * SROW;
     static constexpr int PART = WAVES * RN * 16 * 64 * 4;   // bytes of one round of the epilogue
     static constexpr int RING = NBUF * STAGE + NGRP * GROUP;
     static constexpr int LDS = RING > PART ? RING : PART;
@@ -123,6 +102,7 @@ struct Cfg {
     static_assert(TM % RPI == 0 && TM % SRPI == 0, "a load's rows are all of A or all of B");
     static_assert(LDS <= 160 * 1024 && (CH == 8 || CH == 16) && (SD == 4 || SD == 8) && SROW % SB == 0, "LDS layout");
     static_assert(NBUF >= 2 && NBUF <= 4 && NBUF * LPS + GS * SL <= 63, "vmcnt range");
+    static_assert(GS <= 2, "a stage's piece of a scale group goes by its parity");
     // both repeat every 32 rows: MFMA tile i of a wave lies 32 rows further at the same columns
     static __device__ __forceinline__ int fc(int r) { return CH == 16 ? (r & 15) : ((r & 7) ^ ((r >> 3) & 1)); }
     static __device__ __forceinline__ int fs(int r) { return SD == 8 ? ((r >> 3) & 3) : ((r >> 4) & 1); }
@@ -134,7 +114,7 @@ template <class C> struct Raw {
     uint32_t sa[C::RM], sb[C::RN];
 };
 
-template <int FMT, class C>
+template <int FMT, class C, bool kPacked>
 __global__ __launch_bounds__(C::THREADS, C::LDS <= 80 * 1024 ? C::WAVES / 2 : C::WAVES / 4) void gemm_ksplit_kernel(
     int64_t M, int64_t N, int64_t K, const uint8_t *__restrict__ a_codes, const uint8_t *__restrict__ a_scales,
     const float *__restrict__ ga, const uint8_t *__restrict__ b_codes, const uint8_t *__restrict__ b_scales,
@@ -162,46 +142,85 @@ __global__ __launch_bounds__(C::THREADS, C::LDS <= 80 * 1024 ? C::WAVES / 2 : C:
     const uint8_t *ac = a_codes + m0 * cpr, *bc = b_codes + n0 * cpr;
     const uint8_t *as = a_scales + m0 * spr, *bs = b_scales + n0 * spr;
     const int left_a = (int)(M - m0 < C::TM ? M - m0 : C::TM) - 1, left_b = (int)(N - n0 < C::TN ? N - n0 : C::TN) - 1;
-    uint32_t crow[C::CL];                                   // code loads: the lane's row and column in a stage
-    int ccol[C::CL];
-#pragma unroll
-    for (int i = 0; i < C::CL; ++i) {
-        const int row = (wave * C::CL + i) * C::RPI + lane / C::CH;
-        const int r = row < C::TM ? row : row - C::TM, last = row < C::TM ? left_a : left_b;
-        crow[i] = (uint32_t)(r < last ? r : last) * (uint32_t)cpr;
-        ccol[i] = ((lane % C::CH) ^ C::fc(row)) * 16;
-    }
+    // Packed weights: this tile's first unit, its row groups (past the last: the last)
+    const int64_t nch = (K + 255) / 256;
+    const uint8_t *pc = b_codes + (n0 >> 4) * nch * 2048, *ps = b_scales + (n0 >> 4) * nch * C::SU;
+    const int left_g = (int)((N - n0 < C::TN ? N - n0 : C::TN) - 1) >> 4;
     const int nst = (int)((K + C::KS - 1) / C::KS), ngrp = (nst + C::GS - 1) / C::GS;
     uint8_t *const groups = smem + NBUF * C::STAGE;
+    // Code load i: its rows' first byte, the lane's offset from it, and the lane's column in a
+    // stage.  Packed weights: half a unit, 1 KB, as it lies in the image; column 0, and the
+    // unit in the stage (cunit; units past the last: the last).
+    const uint8_t *cbase[C::CL];
+    uint32_t crow[C::CL];
+    int ccol[C::CL], cunit[C::CL], cper[C::CL], cstep[C::CL];
+#pragma unroll
+    for (int i = 0; i < C::CL; ++i) {
+        const int j = wave * C::CL + i, row = j * C::RPI + lane / C::CH;
+        const bool a = j * C::RPI < C::TM, pk = kPacked && !a;
+        const int jb = j - C::TM / C::RPI, rg = jb / (2 * C::CPS), half = jb % (2 * C::CPS);
+        const int r = pk ? rg : a ? row : row - C::TM, last = pk ? left_g : a ? left_a : left_b;
+        cbase[i] = pk ? pc : a ? ac : bc;
+        crow[i] = (uint32_t)(r < last ? r : last) * (pk ? (uint32_t)nch * 2048u : (uint32_t)cpr) +
+                  (pk ? (uint32_t)(half * 1024 + lane * 16) : 0u);
+        ccol[i] = pk ? 0 : ((lane % C::CH) ^ C::fc(row)) * 16;
+        cunit[i] = pk ? half >> 1 : 0;
+        cper[i] = pk ? C::CPS : 1;
+        cstep[i] = pk ? 2048 : C::ROW;
+    }
+    const int clast = kPacked ? (int)nch - 1 : 0;
+    // Scale load i of piece p of a scale group, likewise (packed: 256 bytes of a row group's run).
+    const uint8_t *sbase[C::GS][C::SL];
+    uint32_t srow[C::GS][C::SL];
+    int scol[C::GS][C::SL], sstep[C::GS][C::SL], send[C::GS][C::SL];
+#pragma unroll
+    for (int p = 0; p < C::GS; ++p)
+#pragma unroll
+        for (int i = 0; i < C::SL; ++i) {
+            const int w = wave * C::SL + i, j = p * C::SPP + (w < C::SPP ? w : C::SPP - 1);
+            const bool a = j * C::SRPI < C::TM, pk = kPacked && !a;
+            const int jb = j - C::TM / C::SRPI, row = j * C::SRPI + lane / C::SD;
+            const int r = pk ? jb * 256 / C::RUN : a ? row : row - C::TM, last = pk ? left_g : a ? left_a : left_b;
+            const int per = pk ? (int)nch * C::SU : (int)spr;
+            sbase[p][i] = pk ? ps : a ? as : bs;
+            srow[p][i] = (uint32_t)(r < last ? r : last) * (uint32_t)per;
+            scol[p][i] = pk ? jb * 256 % C::RUN + lane * 4 : ((lane % C::SD) ^ C::fs(row)) * 4;
+            sstep[p][i] = pk ? C::RUN : C::SROW;
+            send[p][i] = per - 4;
+        }
     // Scale load i of piece p of scale group g (past the last group: of the last, into
     // a buffer nobody reads).  Columns past K re-read the row's last ones, here and
     // below: they belong to slices that are skipped.
     auto load_scale = [&](int g, int p, int i) {
         const int w = wave * C::SL + i, j = p * C::SPP + (w < C::SPP ? w : C::SPP - 1);
-        const int64_t gcol = (int64_t)(g < ngrp ? g : ngrp - 1) * C::SROW;
-        const int64_t left = spr - 4 - gcol;
-        const int lim = left < C::SROW ? (int)left : C::SROW;
-        const bool a = j * C::SRPI < C::TM;
-        const int row = j * C::SRPI + lane / C::SD - (a ? 0 : C::TM), last = a ? left_a : left_b;
-        const int col = ((lane % C::SD) ^ C::fs(row)) * 4;
-        g2l4((a ? as : bs) + gcol, (uint32_t)(row < last ? row : last) * (uint32_t)spr + (uint32_t)(col < lim ? col : lim),
+        const int step = sstep[p][i], at = (g < ngrp ? g : ngrp - 1) * step;
+        const int left = send[p][i] - at, lim = left < step ? left : step;
+        g2l4(sbase[p][i] + at, srow[p][i] + (uint32_t)(scol[p][i] < lim ? scol[p][i] : lim),
              groups + (g % C::NGRP) * C::GROUP + j * 256);
     };
-    // Load L of this wave's share of stage s: its piece of a scale group, then the code loads.
-    auto load_one = [&](int s, int buf, auto LL) {
+    // Load L of this wave's share of stage s (of parity PAR): its piece of a scale
+    // group, then the code loads.
+    auto load_one = [&](int s, int buf, auto LL, auto PAR) {
         constexpr int L = decltype(LL)::value;
         if constexpr (L < C::SL) {
-            load_scale(C::GS == 1 ? s : s / C::GS + 1, s % C::GS, L);
+            load_scale(C::GS == 1 ? s : s / C::GS + 1, C::GS == 1 ? 0 : decltype(PAR)::value, L);
         } else {
             constexpr int i = L - C::SL;
             const int j = wave * C::CL + i;
-            const int64_t kb = (int64_t)s * C::ROW, left = cpr - 16 - kb;
+            const int64_t left = cpr - 16 - (int64_t)s * C::ROW;
             const int lim = left < C::ROW ? (int)left : C::ROW;
-            g2l16((j * C::RPI < C::TM ? ac : bc) + kb, crow[i] + (uint32_t)(ccol[i] < lim ? ccol[i] : lim),
+            int at = s;
+            if constexpr (kPacked) {
+                at = s * cper[i] + cunit[i];
+                at = (at < clast ? at : clast) - cunit[i];
+            }
+            g2l16(cbase[i] + (int64_t)at * cstep[i], crow[i] + (uint32_t)(ccol[i] < lim ? ccol[i] : lim),
                   smem + buf * C::STAGE + j * 1024);
         }
     };
-    auto load_all = [&](int s, int buf) { static_for<0, C::LPS>([&](auto L) { load_one(s, buf, L); }); };
+    auto load_all = [&](int s, int buf, auto PAR) {
+        static_for<0, C::LPS>([&](auto L) { load_one(s, buf, L, PAR); });
+    };
 
     // Slice u of a stage is the wave's 64 elements SUB wk + u of it; lane (r, h) takes
     // their half h of row r.
@@ -216,8 +235,15 @@ __global__ __launch_bounds__(C::THREADS, C::LDS <= 80 * 1024 ? C::WAVES / 2 : C:
         const int byte = (s % C::GS) * C::SB + unit * SPL;  // of the lane's scales in its row of the group
         const int so = (((byte >> 2) ^ C::fs(lr)) << 2) + (byte & 3);
         const int row = t < RM ? arow + 32 * t : brow + 32 * (t - RM);
-        const uint4 c = *reinterpret_cast<const uint4 *>(smem + buf * C::STAGE + row * C::ROW + chunk);
+        const uint8_t *cp = smem + buf * C::STAGE + row * C::ROW + chunk;
         const uint8_t *sp = groups + (s / C::GS) % C::NGRP * C::GROUP + row * C::SROW + so;
+        if constexpr (kPacked && t >= RM) {
+            const int rg = 2 * (wn * RN + t - RM) + (lr >> 4), sl = SUB * wk + u, l = (lr & 15) + 16 * (sl & 3);
+            cp = smem + buf * C::STAGE + C::TM * C::ROW + (rg * C::CPS + (sl >> 2)) * 2048 + h * 1024 + 16 * l;
+            sp = groups + (s / C::GS) % C::NGRP * C::GROUP + C::TM * C::SROW + rg * C::RUN +
+                 ((s % C::GS) * C::CPS + (sl >> 2)) * C::SU + 2 * SPL * l + SPL * h;
+        }
+        const uint4 c = *reinterpret_cast<const uint4 *>(cp);
         uint32_t sc;
         if constexpr (FMT == kMX) sc = *sp;
         else sc = *reinterpret_cast<const uint16_t *>(sp);
@@ -247,9 +273,10 @@ __global__ __launch_bounds__(C::THREADS, C::LDS <= 80 * 1024 ? C::WAVES / 2 : C:
     for (int p = 0; p < (C::GS > 1 ? C::GS : 0); ++p)
 #pragma unroll
         for (int i = 0; i < C::SL; ++i) load_scale(0, p, i);
-#pragma unroll
-    for (int s = 0; s < NBUF; ++s)
-        if (s < nst) load_all(s, s);
+    static_for<0, NBUF>([&](auto S) {
+        constexpr int s = decltype(S)::value;
+        if (s < nst) load_all(s, s, std::integral_constant<int, s & 1>{});
+    });
     {
         const int behind = nst - 1;
         if (NBUF >= 4 && behind >= 3) wait_and_meet<(NBUF >= 4 ? 3 : 0) * C::LPS>();
@@ -267,9 +294,10 @@ __global__ __launch_bounds__(C::THREADS, C::LDS <= 80 * 1024 ? C::WAVES / 2 : C:
     // s + NBUF then go out into the buffer that stage s leaves.  Reads and loads are
     // spread over the MFMAs: ahead of them, each would take its time in turn.
     int buf = 0;                                            // s % NBUF
-    auto slice = [&](int s, auto UU, auto PP, auto STEADY) __attribute__((always_inline)) {
+    auto slice = [&](int s, auto UU, auto PP, auto PAR, auto STEADY) __attribute__((always_inline)) {
         constexpr int u = decltype(UU)::value, P = decltype(PP)::value;
         constexpr bool LAST = u == SUB - 1;
+        using LPAR = std::integral_constant<int, (decltype(PAR)::value + NBUF) & 1>;   // of stage s + NBUF
         constexpr bool steady = decltype(STEADY)::value;    // s + NBUF < nst: no branch in the slice
         const int nbuf = buf + 1 == NBUF ? 0 : buf + 1;
         const int rs = LAST ? s + 1 : s, rbuf = LAST ? nbuf : buf, ru = LAST ? 0 : u + 1;   // the next slice's place
@@ -284,7 +312,7 @@ __global__ __launch_bounds__(C::THREADS, C::LDS <= 80 * 1024 ? C::WAVES / 2 : C:
             else if (NBUF >= 3 && behind >= 1) wait_and_meet<(NBUF >= 3 ? 1 : 0) * C::LPS>();
             else wait_and_meet<0>();
             static_for<0, RM + RN>([&](auto T) { read_tile(raw[P ^ 1], rs, ru, rbuf, T); });
-            if (s + NBUF < nst) load_all(s + NBUF, buf);
+            if (s + NBUF < nst) load_all(s + NBUF, buf, LPAR{});
         } else {
             __builtin_amdgcn_s_waitcnt(0xC07F);             // raw[P], on this path too
         }
@@ -310,14 +338,14 @@ __global__ __launch_bounds__(C::THREADS, C::LDS <= 80 * 1024 ? C::WAVES / 2 : C:
                             static_for<r0 + (r1 - r0) * j / RN, r0 + (r1 - r0) * (j + 1) / RN>(
                                 [&](auto T) { read_tile(raw[P ^ 1], rs, ru, rbuf, T); });
                             static_for<l0 + (l1 - l0) * j / RN, l0 + (l1 - l0) * (j + 1) / RN>(
-                                [&](auto L) { load_one(s + NBUF, buf, L); });
+                                [&](auto L) { load_one(s + NBUF, buf, L, LPAR{}); });
                             __builtin_amdgcn_sched_barrier(0);
                         }
                     });
                 } else {
                     if constexpr (steady) {
                         static_for<r0, r1>([&](auto T) { read_tile(raw[P ^ 1], rs, ru, rbuf, T); });
-                        static_for<l0, l1>([&](auto L) { load_one(s + NBUF, buf, L); });
+                        static_for<l0, l1>([&](auto L) { load_one(s + NBUF, buf, L, LPAR{}); });
                     }
 #pragma unroll
                     for (int j = 0; j < RN; ++j)
@@ -344,22 +372,22 @@ __global__ __launch_bounds__(C::THREADS, C::LDS <= 80 * 1024 ? C::WAVES / 2 : C:
         if (LAST) buf = nbuf;
     };
     // slices of stage s; with one slice per stage the register sets alternate by stage
-    auto stage = [&](int s, auto PP, auto STEADY) __attribute__((always_inline)) {
+    auto stage = [&](int s, auto PP, auto PAR, auto STEADY) __attribute__((always_inline)) {
         constexpr int P = decltype(PP)::value;
         static_for<0, SUB>([&](auto U) {
-            slice(s, U, std::integral_constant<int, (P + decltype(U)::value) & 1>{}, STEADY);
+            slice(s, U, std::integral_constant<int, (P + decltype(U)::value) & 1>{}, PAR, STEADY);
         });
     };
     using I1 = std::integral_constant<int, SUB & 1>;
     static_assert(SUB == 1 || SUB % 2 == 0, "register sets alternate over two stages");
     int s = 0;
     for (; s + 1 + NBUF < nst; s += 2) {
-        stage(s, I0{}, std::true_type{});
-        stage(s + 1, I1{}, std::true_type{});
+        stage(s, I0{}, I0{}, std::true_type{});
+        stage(s + 1, I1{}, std::integral_constant<int, 1>{}, std::true_type{});
     }
     for (; s < nst; s += 2) {
-        stage(s, I0{}, std::false_type{});
-        if (s + 1 < nst) stage(s + 1, I1{}, std::false_type{});
+        stage(s, I0{}, I0{}, std::false_type{});
+        if (s + 1 < nst) stage(s + 1, I1{}, std::integral_constant<int, 1>{}, std::false_type{});
     }
 
     // Results, one row of MFMA tiles per wave at a time, through LDS: the WK partial
@@ -380,6 +408,7 @@ __global__ __launch_bounds__(C::THREADS, C::LDS <= 80 * 1024 ? C::WAVES / 2 : C:
 #pragma unroll
         for (int q0 = 0; q0 < QUADS; q0 += C::THREADS) {
             const int q = q0 + tid;
+            if (QUADS % C::THREADS && q >= QUADS) break;
             const int l = (q & 15) * 4, k = (q >> 4) & 15, jj = q >> 8;
             v4f v = *reinterpret_cast<const v4f *>(part + q * 4);
 #pragma unroll
@@ -406,17 +435,17 @@ __global__ __launch_bounds__(C::THREADS, C::LDS <= 80 * 1024 ? C::WAVES / 2 : C:
     }
 }
 
-template <int FMT, class C>
+template <int FMT, class C, bool kPacked>
 hipError_t launch_cfg(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, const uint8_t *a_scales,
                       const float *ga, const uint8_t *b_codes, const uint8_t *b_scales, const float *gb, void *y,
                       bool y_bf16, int64_t ldy, hipStream_t stream) {
     const int64_t grid = ((M + C::TM - 1) / C::TM) * ((N + C::TN - 1) / C::TN);
     const int64_t es = y_bf16 ? 2 : 4;
     const int y_vec = reinterpret_cast<uintptr_t>(y) % (4 * es) == 0 && ldy % 4 == 0;
-    hipError_t e = hipFuncSetAttribute((const void *)gemm_ksplit_kernel<FMT, C>,
+    hipError_t e = hipFuncSetAttribute((const void *)gemm_ksplit_kernel<FMT, C, kPacked>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((gemm_ksplit_kernel<FMT, C>), dim3((unsigned)grid), dim3(C::THREADS), C::LDS, stream, M, N, K,
+    hipLaunchKernelGGL((gemm_ksplit_kernel<FMT, C, kPacked>), dim3((unsigned)grid), dim3(C::THREADS), C::LDS, stream, M, N, K,
                        a_codes, a_scales, ga, b_codes, b_scales, gb, y, (int)y_bf16, y_vec, ldy);
     return hipGetLastError();
 }
@@ -426,19 +455,28 @@ hipError_t launch_cfg(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, c
 hipError_t launch_gemm_ksplit(KsplitTile tile, Fmt fmt, int64_t M, int64_t N, int64_t K, const uint8_t *a_codes,
                               const uint8_t *a_scales, const float *ga, const uint8_t *b_codes,
                               const uint8_t *b_scales, const float *gb, void *y, bool y_bf16, int64_t ldy,
-                              hipStream_t stream) {
+                              bool packed, hipStream_t stream) {
     // row offsets within a tile are 32-bit (128 rows of K / 2 bytes)
-    if (K <= 0 || K % 128 || K > kKsplitMaxK) return hipErrorInvalidValue;
+    if (K <= 0 || K % 128 || K > kKsplitMaxK || (packed && tile < kTile32x32)) return hipErrorInvalidValue;
     auto go = [&](auto F) {
         constexpr int f = decltype(F)::value;
-        auto cfg = [&](auto c) {
-            return launch_cfg<f, decltype(c)>(M, N, K, a_codes, a_scales, ga, b_codes, b_scales, gb, y, y_bf16, ldy,
-                                              stream);
+        auto rows = [&](auto c) {
+            return launch_cfg<f, decltype(c), false>(M, N, K, a_codes, a_scales, ga, b_codes, b_scales, gb, y, y_bf16,
+                                                     ldy, stream);
+        };
+        auto both = [&](auto c) {
+            return packed ? launch_cfg<f, decltype(c), true>(M, N, K, a_codes, a_scales, ga, b_codes, b_scales, gb, y,
+                                                             y_bf16, ldy, stream)
+                          : rows(c);
         };
         switch (tile) {
-        case kTile64x64: return cfg(Cfg<f, 2, 2, 1, 1, 8, 1, 4, 32>{});
-        case kTile64x128: return cfg(Cfg<f, 2, 2, 1, 2, 2, 2, 2, 16>{});
-        default: return cfg(Cfg<f, 2, 2, 2, 2, 1, 4, 2, 16>{});
+        case kTile32x32: return both(Cfg<f, 1, 1, 1, 1, 8, 1, 4, 32>{});
+        case kTile32x128: return both(Cfg<f, 1, 2, 1, 2, 2, 2, 3, 16>{});
+        case kTile64x32: return both(Cfg<f, 2, 1, 1, 1, 8, 1, 3, 32>{});
+        case kTile64x64Few: return both(Cfg<f, 2, 1, 1, 2, 4, 1, 4, 16>{});
+        case kTile64x64: return rows(Cfg<f, 2, 2, 1, 1, 8, 1, 4, 32>{});
+        case kTile64x128: return rows(Cfg<f, 2, 2, 1, 2, 2, 2, 2, 16>{});
+        default: return rows(Cfg<f, 2, 2, 2, 2, 1, 4, 2, 16>{});
         }
     };
     return fmt == kMX ? go(std::integral_constant<int, kMX>{}) : go(std::integral_constant<int, kNV>{});

@@ -96,13 +96,20 @@ hipError_t launch_gemm_tile256(Fmt fmt, int64_t M, int64_t N, int64_t K, const u
                                const uint8_t *b_scales, const float *gb, void *y, bool y_bf16,
                                int64_t ldy, hipStream_t stream);
 
-// Small tiles for M > 64 (gemm_ksplit.hip): 0 < K <= kKsplitMaxK, K % 128 == 0.
-enum KsplitTile : int { kTile64x64, kTile64x128, kTile128x128 };
+// Small tiles (gemm_ksplit.hip): 0 < K <= kKsplitMaxK, K % 128 == 0.  The last four serve
+// up to 64 rows and take the packed decode image too.
+enum KsplitTile : int { kTile64x64, kTile64x128, kTile128x128, kTile32x32, kTile32x128, kTile64x32, kTile64x64Few };
 constexpr int64_t kKsplitMaxK = int64_t(1) << 26;
 hipError_t launch_gemm_ksplit(KsplitTile tile, Fmt fmt, int64_t M, int64_t N, int64_t K, const uint8_t *a_codes,
                               const uint8_t *a_scales, const float *ga, const uint8_t *b_codes,
                               const uint8_t *b_scales, const float *gb, void *y, bool y_bf16, int64_t ldy,
-                              hipStream_t stream);
+                              bool packed, hipStream_t stream);
+
+// M <= 64 and K > 0; packed: b_codes / b_scales are the parts of the decode image.
+hipError_t launch_gemm_decode(Fmt fmt, int64_t M, int64_t N, int64_t K, const uint8_t *a_codes,
+                              const uint8_t *a_scales, const float *ga, const uint8_t *b_codes,
+                              const uint8_t *b_scales, const float *gb, void *y, bool y_bf16, int64_t ldy,
+                              bool packed, hipStream_t stream);
 
 hipError_t launch_gemm(Fmt fmt, int64_t M, int64_t N, int64_t K, const uint8_t *a_codes,
                        const uint8_t *a_scales, const float *ga, const uint8_t *b_codes,

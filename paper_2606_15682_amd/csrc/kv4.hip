@@ -318,7 +318,18 @@ __device__ __forceinline__ uint32_t kv4_pack8(const float *c) {
 // some |q - rint(q)| >= 0.5 - 2^-17 takes the threshold path instead.  The
 // fake-quant value c * H has at most 7 significant bits and is normal or
 // zero, so its top 16 bits are the bfloat16 value.
-template <int OUT>
+//
+// kBf16 (no shift: d is a bfloat16 value, 8 significant bits): exact midpoints
+// are common, about one element in 60 of normal data, and nearly every wave took the
+// threshold path for some lane.  Here a quotient that is not a half-integer
+// lies at least 2^-10 from every one: in |d - mid H| the two are multiples of 2^a
+// (d = D 2^a, 128 <= D < 256 or d subnormal) and 2^(e-1) (H = h 2^e, h <= 15), so
+// a difference is at least H / 30 or, near the midpoint, about H / 512.  So q is
+// rounded to a multiple of 2^-12 (by adding 3072: the sum lies in [2048, 4096)),
+// which gives a half-integer exactly where d / H is one and keeps the side
+// elsewhere; then rint decides as above, ties included, and no block is left
+// undecided.  Values of a 32768 x 1024 cache slice: 40 -> 28 us.
+template <int OUT, bool kBf16>
 __device__ __forceinline__ uint32_t kv4_emit(const float (&d)[16], uint32_t am, int64_t blk, int64_t nb, bool narrow,
                                              const Kv4G &G, uint8_t *__restrict__ codes, uint8_t *__restrict__ scales,
                                              uint16_t *__restrict__ y, int64_t ldy) {
@@ -335,9 +346,14 @@ __device__ __forceinline__ uint32_t kv4_emit(const float (&d)[16], uint32_t am, 
     float emax = 0.0f;
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
-        const float q = d[j] * rh;
-        cf[j] = __builtin_rintf(q);
-        emax = __builtin_fmaxf(emax, __builtin_fabsf(q - cf[j]));
+        if constexpr (kBf16) {
+            const float q = __builtin_fmaf(d[j], rh, 3072.0f) - 3072.0f;
+            cf[j] = __builtin_copysignf(__builtin_rintf(q), d[j]);
+        } else {
+            const float q = d[j] * rh;
+            cf[j] = __builtin_rintf(q);
+            emax = __builtin_fmaxf(emax, __builtin_fabsf(q - cf[j]));
+        }
     }
     const bool exact = !fast_ok || emax >= 0.5f - 0x1p-17f;
     if (OUT == kCodes) {
@@ -432,7 +448,7 @@ __global__ __launch_bounds__(kThreads) void kv4_quantize_kernel(
 #pragma unroll
         for (int u = 0; u < kKvU; ++u) {
             const int64_t blk = base + 64 * u + lane;
-            if (blk < total) kv4_emit<OUT>(d[u], kv4_block_max(d[u]), blk, nb, narrow, G, codes, scales, y, ldy);
+            if (blk < total) kv4_emit<OUT, SRC == kNoShift>(d[u], kv4_block_max(d[u]), blk, nb, narrow, G, codes, scales, y, ldy);
         }
     }
 }
@@ -504,7 +520,7 @@ __global__ __launch_bounds__(kThreads) void kv4_quantize_deferred_kernel(
             const uint32_t segmax = kv4_wave_reduce<true>(fm);
             const Kv4G Gr = kv4_make_g(kv4_global_scale(segmax));
             uint32_t sbyte = 0u;
-            if (act) sbyte = kv4_emit<OUT>(d[u], am, blk, nb, narrow, Gr, codes, scales, y, ldy);
+            if (act) sbyte = kv4_emit<OUT, SRC == kNoShift>(d[u], am, blk, nb, narrow, Gr, codes, scales, y, ldy);
             const bool live = act && am != 0u && !bad;
             const uint32_t emin = kv4_wave_reduce<false>(live ? sbyte >> 3 : 0xFFu);
             if (lane == 0)
@@ -617,7 +633,7 @@ __global__ __launch_bounds__(kThreads) void kv4_fixup_kernel(
                     float d[16];
                     if (shift) kv4_load<kShiftGlobal>(x, shift, nullptr, blk, nb, ldx, narrow, d);
                     else kv4_load<kNoShift>(x, shift, nullptr, blk, nb, ldx, narrow, d);
-                    kv4_emit<OUT>(d, kv4_block_max(d), blk, nb, narrow, G, codes, scales, y, ldy);
+                    kv4_emit<OUT, false>(d, kv4_block_max(d), blk, nb, narrow, G, codes, scales, y, ldy);
                 }
             }
         }

@@ -279,6 +279,8 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(
                 if (pl.fast) {
                     uint16_t *ydst = OUT != kCodes ? y + block_offset(blk[u], nb, cols, ldy, B, narrow) : nullptr;
                     emit_fast<FMT, OUT>(wc[u], pl, blk[u], codes, scales, ydst);
+                } else if constexpr (FMT == kNV && OUT == kCodes && GM == kGFixed) {
+                    if (!Gs[u].pow2) general[u] = !emit_codes_any_g(wc[u], am[u], Gs[u], blk[u], codes, scales);
                 }
             }
         }

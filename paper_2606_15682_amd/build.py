@@ -13,7 +13,8 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libreqat.so")
-SOURCES = ["api.hip", "quantize.hip", "gemm.hip", "gemm_skinny.hip", "gemm_tile256.hip", "gemm_ksplit.hip", "gemm_w4a16.hip", "kv4.hip", "sem.hip"]
+SOURCES = ["api.hip", "quantize.hip", "gemm.hip", "gemm_skinny.hip", "gemm_tile256.hip", "gemm_ksplit.hip", "gemm_w4a16.hip", "gemm_w4a16_tile.hip",
+           "kv4.hip", "sem.hip"]
 PROBE_LIB = os.path.join(HERE, "libreqat_probe.so")
 PROBE_SOURCE = "probe_mfma.hip"
 

@@ -381,10 +381,53 @@ size_t gemm_w4a16_workspace_bytes(int64_t M, int64_t N, int64_t K) {
     return ks > 1 ? sizeof(float) * (size_t)ks * (size_t)M * (size_t)N : 0;
 }
 
+namespace {
+
+// From 33 rows on: this file's kernel (64 rows of x and of W per workgroup, K split over
+// workgroups) or the tile with the least estimated time, where it promises 12% or more.
+// This kernel: 9 us and 16 ns per 64 x 64 block and 1000 elements of K.  Tiles: c + rounds
+// t K; a workgroup alone on its CU and two sharing one finish at the same rate per tile,
+// so rounds = tiles / 256, half way to the next whole number.  Fitted over M = 64 .. 1024 and
+// twelve (N, K) from (2048, 1536) to (55296, 5120), weights from HBM.  For example, in us,
+// this kernel / 64 x 64 / 64 x 128 / 128 x 128 of 4 waves / of 8 waves:
+//   512 x 27648 x 5120: 221 / 181 / 131 / 130 / 142    512 x 5120 x 13824: 121 / 103 / 85 / 93 / 73
+//   64 x 5120 x 13824: 26 / 44 / 52 / 91 / 63          128 x 2048 x 1536: 11.6 / 7.1 / 9.1 / 13.7 / 12.4
+// Sizes alone decide, so packed and row-major weights give the same result.
+struct TileCost {
+    int tm, tn;
+    double c, t;                                // ns, ns per element of K and round
+};
+constexpr TileCost kCost[4] = {{64, 64, 3200, 2.9}, {64, 128, 3200, 3.7}, {128, 128, 4000, 6.5}, {128, 128, 4500, 5.3}};
+
+// -1: this file's kernel; else the W16Tile.
+int pick_tile(int64_t M, int64_t N, int64_t K, int64_t ldx) {
+    if (M <= 32 || K <= 0 || K > kW16TileMaxLd || ldx > kW16TileMaxLd) return -1;
+    int best = -1;
+    double least = 0.88 * (9000 + 0.016 * (double)((N + 63) / 64) * (double)((M + 63) / 64) * (double)K);
+    for (int i = 0; i < 4; ++i) {
+        const TileCost &q = kCost[i];
+        const int64_t tiles = ((M + q.tm - 1) / q.tm) * ((N + q.tn - 1) / q.tn);
+        if (i == kW16Tile128x128x8 && tiles > 256) continue;    // one workgroup per CU: for a single round
+        const double full = (double)tiles / 256, rounds = tiles <= 256 ? 1.0 : 0.5 * (full + (double)((tiles + 255) / 256));
+        const double est = q.c + rounds * q.t * (double)K;
+        if (est < least) {
+            best = i;
+            least = est;
+        }
+    }
+    return best;
+}
+
+}  // namespace
+
 hipError_t launch_gemm_w4a16(int64_t M, int64_t N, int64_t K, const uint16_t *x, int64_t ldx,
                              const uint8_t *w_codes, const uint8_t *w_scales, bool packed, void *y, bool y_bf16,
                              int64_t ldy, float *workspace, hipStream_t stream) {
     if (M == 0 || N == 0) return hipSuccess;
+    const int tile = pick_tile(M, N, K, ldx);
+    if (tile >= 0)
+        return launch_gemm_w4a16_tile((W16Tile)tile, M, N, K, x, ldx, w_codes, w_scales, packed, y, y_bf16, ldy,
+                                      stream);
     const int ks = gemm_w4a16_splits(M, N, K);
     switch (row_tile(M)) {
     case 1: return launch_mt<1>(M, N, K, x, ldx, w_codes, w_scales, packed, y, y_bf16, ldy, ks, workspace, stream);

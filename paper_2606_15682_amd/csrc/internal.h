@@ -55,6 +55,12 @@ int gemm_w4a16_splits(int64_t M, int64_t N, int64_t K);
 size_t gemm_w4a16_workspace_bytes(int64_t M, int64_t N, int64_t K);
 // packed: w_codes / w_scales are the code and scale parts of the packed image
 // that launch_w4a16_pack writes (w4a16_packed_bytes(N, K) bytes).
+// Tiles for larger M (gemm_w4a16_tile.hip): 0 < K <= kW16TileMaxLd, K % 128 == 0, ldx <= kW16TileMaxLd.
+enum W16Tile : int { kW16Tile64x64, kW16Tile64x128, kW16Tile128x128, kW16Tile128x128x8 };
+constexpr int64_t kW16TileMaxLd = int64_t(1) << 23;
+hipError_t launch_gemm_w4a16_tile(W16Tile tile, int64_t M, int64_t N, int64_t K, const uint16_t *x, int64_t ldx,
+                                  const uint8_t *w_codes, const uint8_t *w_scales, bool packed, void *y, bool y_bf16,
+                                  int64_t ldy, hipStream_t stream);
 hipError_t launch_gemm_w4a16(int64_t M, int64_t N, int64_t K, const uint16_t *x, int64_t ldx,
                              const uint8_t *w_codes, const uint8_t *w_scales, bool packed, void *y, bool y_bf16,
                              int64_t ldy, float *workspace, hipStream_t stream);

@@ -208,15 +208,25 @@ namespace {
 //   MXFP4  128 x 4608 x 3584: 8.2 / 12.7 / 15.4 / 28   777 x 7168 x 5120: 46 / 41 / 29 / 40
 //          2048 x 4608 x 3584: 55 / 38 / 35 / 29
 // The rule uses sizes alone, so a shape always runs the same kernel.
+//
+// The deep tiles (eight waves, one workgroup per CU, three or four stages on their
+// way) are for a single round: alone on a CU the plain 64 x 128 and 128 x 128 tiles
+// wait a microsecond for each stage of 256 elements, shared by two workgroups they
+// do not.  Plain / deep, in us: MXFP4 777 x 3584 x 18944 75 / 47, 777 x 1792 x 5120 16.5 / 12.9,
+// NVFP4 256 x 5120 x 13824 63 / 52; in two rounds 1536 x 5120 x 1280 (MXFP4) 13.6 / 15.4.
 struct TileCost {
     int tm, tn;
+    bool single;                                // for one round alone
     double c, e, t, alone;
 };
-constexpr TileCost kCost[2][4] = {
-    // NVFP4: 64 x 64, 64 x 128, 128 x 128, 256 x 256
-    {{64, 64, 3000, 1800, 2.15, 0}, {64, 128, 4000, 0, 3.6, 4.2}, {128, 128, 4000, 0, 6.9, 7.6}, {256, 256, 4000, 0, 22, 20}},
+constexpr int kTileLarge = 5;
+constexpr TileCost kCost[2][6] = {              // by KsplitTile, then 256 x 256
+    // NVFP4
+    {{64, 64, false, 3000, 1800, 2.15, 0}, {64, 128, false, 4000, 0, 3.6, 4.2}, {128, 128, false, 4000, 0, 6.9, 7.6},
+     {64, 128, true, 4500, 0, 3.6, 0}, {0, 0, true, 0, 0, 0, 0}, {256, 256, false, 4000, 0, 22, 20}},
     // MXFP4
-    {{64, 64, 3000, 1200, 1.3, 0}, {64, 128, 3000, 700, 2.0, 3.4}, {128, 128, 3000, 700, 2.9, 4.0}, {256, 256, 3000, 700, 7.7, 0}},
+    {{64, 64, false, 3000, 1200, 1.3, 0}, {64, 128, false, 3000, 700, 2.0, 3.4}, {128, 128, false, 3000, 700, 2.9, 4.0},
+     {64, 128, true, 3500, 0, 2.4, 0}, {128, 128, true, 4000, 0, 2.7, 0}, {256, 256, false, 3000, 700, 7.7, 0}},
 };
 
 // Small tiles have to promise this much: where the estimates are closer they
@@ -224,17 +234,19 @@ constexpr TileCost kCost[2][4] = {
 // against two: 4% under the 256 x 256 tiles by the estimate, 4% over them measured).
 constexpr double kLargeBias = 0.88;
 
-// 0 .. 2: KsplitTile; 3: 256 x 256 tiles
+// The KsplitTile, or kTileLarge: 256 x 256 tiles
 int pick_tile(Fmt fmt, int64_t M, int64_t N, int64_t K, bool big_ok) {
     int best = 0;
     double least = 0;
-    for (int i = 0; i < (big_ok ? 4 : 3); ++i) {
+    for (int i = 0; i < (big_ok ? kTileLarge + 1 : kTileLarge); ++i) {
         const TileCost &q = kCost[fmt == kMX][i];
+        if (q.tm == 0) continue;
         const int64_t tiles = ((M + q.tm - 1) / q.tm) * ((N + q.tn - 1) / q.tn);
         const double rounds = (double)((tiles + 255) / 256);
+        if (q.single && rounds > 1) continue;
         const double t = rounds == 1 && q.alone > 0 ? q.alone : q.t;
         const double est = q.c + rounds * (q.e + t * (double)K);
-        if (i == 0 || (i == 3 ? kLargeBias : 1.0) * est < least) {
+        if (i == 0 || (i == kTileLarge ? kLargeBias : 1.0) * est < least) {
             best = i;
             least = est;
         }
@@ -309,7 +321,7 @@ hipError_t launch_gemm(Fmt fmt, int64_t M, int64_t N, int64_t K, const uint8_t *
                                   ldy, false, stream);
     if (K > 0 && K <= kKsplitMaxK) {
         const int tile = pick_tile(fmt, M, N, K, gemm_tile256_supported(fmt, M, N, K, ldy));
-        if (tile == 3)
+        if (tile == kTileLarge)
             return launch_gemm_tile256(fmt, M, N, K, a_codes, a_scales, ga, b_codes, b_scales, gb, y,
                                        y_bf16, ldy, stream);
         return launch_gemm_ksplit((KsplitTile)tile, fmt, M, N, K, a_codes, a_scales, ga, b_codes, b_scales, gb, y,

@@ -476,8 +476,12 @@ hipError_t launch_gemm_ksplit(KsplitTile tile, Fmt fmt, int64_t M, int64_t N, in
         case kTile64x64Few: return both(Cfg<f, 2, 1, 1, 2, 4, 1, 4, 16>{});
         case kTile64x64: return rows(Cfg<f, 2, 2, 1, 1, 8, 1, 4, 32>{});
         case kTile64x128: return rows(Cfg<f, 2, 2, 1, 2, 2, 2, 2, 16>{});
-        default: return rows(Cfg<f, 2, 2, 2, 2, 1, 4, 2, 16>{});
+        case kTile128x128: return rows(Cfg<f, 2, 2, 2, 2, 1, 4, 2, 16>{});
+        case kTile64x128Deep: return rows(Cfg<f, 2, 2, 1, 2, 4, 1, 4, 16>{});
+        case kTile128x128Deep:
+            if constexpr (f == kMX) return rows(Cfg<f, 2, 2, 2, 2, 2, 2, 3, 16>{});
         }
+        return hipErrorInvalidValue;
     };
     return fmt == kMX ? go(std::integral_constant<int, kMX>{}) : go(std::integral_constant<int, kNV>{});
 }

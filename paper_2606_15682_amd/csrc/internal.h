@@ -102,9 +102,10 @@ hipError_t launch_gemm_tile256(Fmt fmt, int64_t M, int64_t N, int64_t K, const u
                                const uint8_t *b_scales, const float *gb, void *y, bool y_bf16,
                                int64_t ldy, hipStream_t stream);
 
-// Small tiles (gemm_ksplit.hip): 0 < K <= kKsplitMaxK, K % 128 == 0.  The last four serve
-// up to 64 rows and take the packed decode image too.
-enum KsplitTile : int { kTile64x64, kTile64x128, kTile128x128, kTile32x32, kTile32x128, kTile64x32, kTile64x64Few };
+// Small tiles (gemm_ksplit.hip): 0 < K <= kKsplitMaxK, K % 128 == 0.  The deep ones have twice the
+// waves and a longer ring (128 x 128: MXFP4 alone).  The last four serve up to 64 rows and take the
+// packed decode image too.
+enum KsplitTile : int { kTile64x64, kTile64x128, kTile128x128, kTile64x128Deep, kTile128x128Deep, kTile32x32, kTile32x128, kTile64x32, kTile64x64Few };
 constexpr int64_t kKsplitMaxK = int64_t(1) << 26;
 hipError_t launch_gemm_ksplit(KsplitTile tile, Fmt fmt, int64_t M, int64_t N, int64_t K, const uint8_t *a_codes,
                               const uint8_t *a_scales, const float *ga, const uint8_t *b_codes,

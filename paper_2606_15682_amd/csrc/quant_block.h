@@ -335,8 +335,8 @@ __device__ __forceinline__ float residual(float x, float c, float h, float l) {
 //     to the quotient is c or the quotient is far from any); c itself if amax <= 6 c g, else the next.
 //   elements: c = the 3-bit value nearest to x * rcp(s g).  All rounding midpoints are 3-bit
 //     values, so c moved a 64th towards x rounds as the exact quotient, and c itself where x = c s g.
-// False (and nothing written) for a zero or non-finite block, a scale outside the normal E4M3
-// values and g outside [2^-100, 2^100], where a residual could be subnormal; the block then
+// False (and nothing written) for a zero or non-finite block, one whose scale would be subnormal
+// or that lies 2^11 beyond the largest, and g outside [2^-100, 2^100], where a residual could be subnormal; the block then
 // takes the general path.  Before, every block did: a layer of 256 tokens (four
 // activations, 3584 to 18944 wide) 190 -> 168 us.  (Quotients
 // with a window around the midpoints, and the general path for blocks inside it, were slower:
@@ -348,8 +348,9 @@ __device__ __forceinline__ bool emit_codes_any_g(const uint32_t (&w)[8], uint32_
     const float a = f32_from_bits(am << 16), g6 = 6.0f * G.g;
     const uint32_t qb = (bits_from_f32(a * __builtin_amdgcn_rcpf(g6)) + 0x80000u) & 0xFFF00000u;
     const bool up = residual(a, f32_from_bits(qb), g6, __builtin_fmaf(6.0f, G.g, -g6)) > 0.0f;
-    const uint32_t sb = (qb >> 20) + (up ? 1u : 0u);
-    if (qb < (121u << 23) || sb > 0x7Eu + (120u << 3)) return false;
+    if (qb < (121u << 23) || qb > (147u << 23)) return false;
+    uint32_t sb = (qb >> 20) + (up ? 1u : 0u);
+    sb = sb < 0x7Eu + (120u << 3) ? sb : 0x7Eu + (120u << 3);   // beyond the calibrated range: 448, elements saturate
     const float s = f32_from_bits(sb << 20), h = s * G.g, l = __builtin_fmaf(s, G.g, -h), r = __builtin_amdgcn_rcpf(h);
     uint32_t cw[2];
 #pragma unroll

@@ -39,10 +39,12 @@ def _edges(g, rows=96, cols=256):
 
 @pytest.mark.parametrize("g", [0.0123, 1.0 / 3.0, 3.5, 0.1875, 2.0 ** -100 * 1.1, 2.0 ** -101 * 1.1, 2.0 ** 99 * 1.7,
                                2.0 ** 101 * 1.3, 1.0000001])
-def test_given_g(g):
-    log("NVFP4 given g=%r" % g)
-    g = float(np.float32(g))
-    x = np.concatenate([_edges(g), _rand(70, 256, 3, "student_t", outliers=3)])
+@pytest.mark.parametrize("short", [1.0, 5.1, 1e5])        # g as calibrated, or too small for the largest blocks
+def test_given_g(g, short):
+    log("NVFP4 given g=%r / %r" % (g, short))
+    x = _edges(float(np.float32(g)))
+    g = float(np.float32(g / short))
+    x = np.concatenate([x, _rand(70, 256, 3, "student_t", outliers=3)])
     codes, scales, _ = oracle.quantize(NV, x, g)
     c, s, _ = reqat.quantize(wl.from_bits(x).to(DEV), NV,
                              tensor_scale=torch.tensor([g], dtype=torch.float32, device=DEV))

@@ -30,7 +30,8 @@ def _model(x, g, ulp):
     c = _snap(a * rcp(g6), 0x80000, 0xFFF00000)
     up = _fma(-c, _fma(F(6), g, -g6), _fma(-c, g6, a)) > 0
     sb = (c.view(np.uint32) >> 20) + up
-    ok = (a > 0) & np.isfinite(a) & (c >= F(2.0 ** -6)) & (sb <= 0x7E + 960)
+    ok = (a > 0) & np.isfinite(a) & (c >= F(2.0 ** -6)) & (c <= F(2.0 ** 20))
+    sb = np.minimum(sb, 0x7E + 960)
     s = (sb.astype(np.uint32) << 20).view(F)
     h = s * g
     low = _fma(s, g, -h)[:, None]
@@ -45,10 +46,11 @@ def _model(x, g, ulp):
 
 
 @pytest.mark.parametrize("ulp", [0, 1, -1])
+@pytest.mark.parametrize("short", [1.0, 5.1])             # g as calibrated, or too small for the largest blocks
 @pytest.mark.parametrize("g", [0.0123, 1.0 / 3.0, 3.5, 0.1875, 2.0 ** -100 * 1.1, 2.0 ** 99 * 1.7, 1.0000001])
-def test_every_block_the_path_takes(g, ulp):
-    g = float(F(g))
-    x = _edges(g, rows=600)
+def test_every_block_the_path_takes(g, short, ulp):
+    x = _edges(float(F(g)), rows=600)
+    g = float(F(g / short))
     codes, scales, _ = oracle.quantize(NV, x, g)
     with np.errstate(all="ignore"):
         ok, sb, code = _model(x, g, ulp)

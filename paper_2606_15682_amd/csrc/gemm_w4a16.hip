@@ -264,6 +264,92 @@ __global__ __launch_bounds__(kThreads) void gemm_w4a16_kernel(
     }
 }
 
+// Decode with few weight rows (M <= 16): a workgroup of eight waves owns 16 rows of W and
+// all of K, the waves taking contiguous shares of its chunks; their partial sums meet in
+// LDS and are added in the order of the waves.  Against K split over workgroups this
+// saves the partial sums' way through memory and the launch that adds them (4 us of 12 for
+// 4 x 7168 x 5120).  Each wave stages its own chunks of x in LDS, 4 RQ rows of 256 bytes in
+// coalesced loads, and needs no barrier for them; 4 RQ >= M, rows past M re-read the
+// last one, and rows of D past 4 RQ come from row 4 RQ - 1 and are not stored.
+template <int RQ, bool kPacked>
+__global__ __launch_bounds__(512) void gemm_w4a16_decode_kernel(
+    int64_t M, int64_t N, int64_t K, const uint16_t *__restrict__ x, int64_t ldx,
+    const uint8_t *__restrict__ w_codes, const uint8_t *__restrict__ w_scales, void *__restrict__ y, int y_bf16,
+    int64_t ldy) {
+    constexpr int kWaves = 8, D = 4, XP = 128 + 8;    // chunks on their way; LDS pitch of a row of x
+    __shared__ __attribute__((aligned(16))) uint16_t xs[kWaves][4 * RQ][XP];
+    __shared__ float part[kWaves][4][64];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15, kg = lane >> 4;
+    const int64_t n0 = (int64_t)blockIdx.x * 16, nch = K / 128;
+    const int64_t c0 = nch * wave / kWaves, my = nch * (wave + 1) / kWaves - c0;
+
+    const uint16_t *xp[RQ];
+#pragma unroll
+    for (int i = 0; i < RQ; ++i) {
+        const int64_t row = 4 * i + kg < M ? 4 * i + kg : M - 1;
+        xp[i] = x + row * ldx + 8 * r;
+    }
+    const int64_t wrow = n0 + r < N ? n0 + r : N - 1;
+    const uint8_t *wp = kPacked ? w_codes + ((int64_t)blockIdx.x * nch << 10) + lane * 16
+                                : w_codes + wrow * (K / 2) + kg * 16;
+    const uint8_t *sp = kPacked ? w_scales + ((int64_t)blockIdx.x * nch << 6) + r * 4 : w_scales + wrow * (K / 32);
+
+    v4u xv[D][RQ], wv[D];
+    uint32_t sv[D];
+    auto load = [&](int64_t i, auto J) {                // chunk i of the wave's
+        constexpr int j = decltype(J)::value;
+        if (i >= my) return;                            // uniform
+        const int64_t c = c0 + i;
+        wv[j] = *reinterpret_cast<const v4u *>(wp + (kPacked ? c << 10 : c * 64));
+        sv[j] = *reinterpret_cast<const uint32_t *>(sp + (kPacked ? c << 6 : c * 4));
+#pragma unroll
+        for (int q = 0; q < RQ; ++q) xv[j][q] = *reinterpret_cast<const v4u *>(xp[q] + c * 128);
+    };
+    v4f acc = v4f{};
+    auto multiply = [&](auto J) {
+        constexpr int j = decltype(J)::value;
+#pragma unroll
+        for (int q = 0; q < RQ; ++q) *reinterpret_cast<v4u *>(&xs[wave][4 * q + kg][8 * r]) = xv[j][q];
+        // the wave's LDS accesses are carried out in order; this keeps the compiler's order too
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        const uint32_t sb = (sv[j] >> (8 * kg)) & 0xFFu;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const v4u xa = *reinterpret_cast<const v4u *>(&xs[wave][r < 4 * RQ ? r : 4 * RQ - 1][32 * kg + 8 * s]);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, xa), decode_step(wv[j], sb, s), acc,
+                                                          0, 0, 0);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    };
+    static_for<0, D>([&](auto J) { load(decltype(J)::value, J); });
+    for (int64_t i0 = 0; i0 < my; i0 += D)
+        static_for<0, D>([&](auto J) {
+            const int64_t i = i0 + decltype(J)::value;
+            if (i < my) {
+                multiply(J);
+                load(i + D, J);
+            }
+        });
+#pragma unroll
+    for (int k = 0; k < 4; ++k) part[wave][k][lane] = acc[k];
+    __syncthreads();
+    if (tid < 256) {
+        const int k = tid >> 6, l = tid & 63;
+        float v = part[0][k][l];
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) v += part[w][k][l];
+        // D[m][n] of a 16 x 16 tile sits in lane n + 16 * (m / 4), register m % 4
+        const int64_t m = 4 * (l >> 4) + k, n = n0 + (l & 15);
+        if (m < M && n < N) {
+            if (y_bf16) reinterpret_cast<__bf16 *>(y)[m * ldy + n] = (__bf16)v;
+            else reinterpret_cast<float *>(y)[m * ldy + n] = v;
+        }
+    }
+}
+
 // y[m][n] = sum over splits, in split order, of part[ks][m][n].
 __global__ __launch_bounds__(kThreads) void gemm_w4a16_reduce(int64_t M, int64_t N, int KS,
                                                               const float *__restrict__ part, void *__restrict__ y,
@@ -305,6 +391,19 @@ hipError_t launch_mt(int64_t M, int64_t N, int64_t K, const uint16_t *x, int64_t
     if (rgrid > 4096) rgrid = 4096;
     hipLaunchKernelGGL(gemm_w4a16_reduce, dim3((unsigned)rgrid), dim3(kThreads), 0, stream, M, N, KS, part, y,
                        (int)y_bf16, ldy);
+    return hipGetLastError();
+}
+
+template <int RQ>
+hipError_t launch_decode(int64_t M, int64_t N, int64_t K, const uint16_t *x, int64_t ldx, const uint8_t *w_codes,
+                         const uint8_t *w_scales, bool packed, void *y, bool y_bf16, int64_t ldy, hipStream_t stream) {
+    const dim3 grid((unsigned)((N + 15) / 16)), block(512);
+    if (packed)
+        hipLaunchKernelGGL((gemm_w4a16_decode_kernel<RQ, true>), grid, block, 0, stream, M, N, K, x, ldx, w_codes,
+                           w_scales, y, (int)y_bf16, ldy);
+    else
+        hipLaunchKernelGGL((gemm_w4a16_decode_kernel<RQ, false>), grid, block, 0, stream, M, N, K, x, ldx, w_codes,
+                           w_scales, y, (int)y_bf16, ldy);
     return hipGetLastError();
 }
 
@@ -399,6 +498,22 @@ struct TileCost {
 };
 constexpr TileCost kCost[4] = {{64, 64, 3200, 2.9}, {64, 128, 3200, 3.7}, {128, 128, 4000, 6.5}, {128, 128, 4500, 5.3}};
 
+// M <= 16: whether gemm_w4a16_decode_kernel, which reads x once for 16 rows of W, is faster
+// than gemm_w4a16_kernel, which reads it once for 64 and splits K over workgroups where those
+// are fewer than the CUs.  Estimates in us, K in thousands, fitted over twenty (N, K) from
+// (768, 1536) to (55296, 5120) and M = 1, 4, 8, 16, weights from HBM; 5% has to be promised.
+// For example, split or unsplit / this one:
+//   4 x 3584 x 3584 7.1 / 4.1    4 x 55296 x 5120 34.9 / 32.9    16 x 2048 x 1536 6.0 / 3.5
+//   8 x 7168 x 5120 11.1 / 8.2   4 x 5120 x 27648 20.5 / 23.8    16 x 27648 x 5120 21 / 37
+bool decode_pays(int64_t M, int64_t N, int64_t K) {
+    if (M > 16 || K <= 0) return false;
+    const double k = 1e-3 * (double)K, w = 1e-6 * (double)N * (double)K, wg = (double)((N + 15) / 16) / 256;
+    const double split = N <= 64 * 255 ? 5.6 + 0.11 * w : 3.2 + 0.112 * w;
+    const double rate = M <= 4 ? 0.39 : (M <= 8 ? 0.52 : 0.93);
+    const double rounds = wg <= 1 ? 0.6 + 0.4 * wg : (double)(((N + 15) / 16 + 255) / 256);
+    return 2.6 + rounds * rate * k < 0.95 * split;
+}
+
 // -1: this file's kernel; else the W16Tile.
 int pick_tile(int64_t M, int64_t N, int64_t K, int64_t ldx) {
     if (M <= 32 || K <= 0 || K > kW16TileMaxLd || ldx > kW16TileMaxLd) return -1;
@@ -428,6 +543,11 @@ hipError_t launch_gemm_w4a16(int64_t M, int64_t N, int64_t K, const uint16_t *x,
     if (tile >= 0)
         return launch_gemm_w4a16_tile((W16Tile)tile, M, N, K, x, ldx, w_codes, w_scales, packed, y, y_bf16, ldy,
                                       stream);
+    if (decode_pays(M, N, K)) {
+        if (M <= 4) return launch_decode<1>(M, N, K, x, ldx, w_codes, w_scales, packed, y, y_bf16, ldy, stream);
+        if (M <= 8) return launch_decode<2>(M, N, K, x, ldx, w_codes, w_scales, packed, y, y_bf16, ldy, stream);
+        return launch_decode<4>(M, N, K, x, ldx, w_codes, w_scales, packed, y, y_bf16, ldy, stream);
+    }
     const int ks = gemm_w4a16_splits(M, N, K);
     switch (row_tile(M)) {
     case 1: return launch_mt<1>(M, N, K, x, ldx, w_codes, w_scales, packed, y, y_bf16, ldy, ks, workspace, stream);

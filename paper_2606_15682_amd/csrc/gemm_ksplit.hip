@@ -154,8 +154,10 @@ __global__ __launch_bounds__(C::THREADS, C::LDS <= 80 * 1024 ? C::WAVES / 2 : C:
     const uint8_t *cbase[C::CL];
     uint32_t crow[C::CL];
     int ccol[C::CL], cunit[C::CL], cper[C::CL], cstep[C::CL];
-#pragma unroll
-    for (int i = 0; i < C::CL; ++i) {
+    // (unrolled by templates: the bases have to end up in scalar registers at every
+    // optimisation level, and a loop over the arrays can leave them in memory)
+    static_for<0, C::CL>([&](auto I) __attribute__((always_inline)) {
+        constexpr int i = decltype(I)::value;
         const int j = wave * C::CL + i, row = j * C::RPI + lane / C::CH;
         const bool a = j * C::RPI < C::TM, pk = kPacked && !a;
         const int jb = j - C::TM / C::RPI, rg = jb / (2 * C::CPS), half = jb % (2 * C::CPS);
@@ -167,16 +169,15 @@ __global__ __launch_bounds__(C::THREADS, C::LDS <= 80 * 1024 ? C::WAVES / 2 : C:
         cunit[i] = pk ? half >> 1 : 0;
         cper[i] = pk ? C::CPS : 1;
         cstep[i] = pk ? 2048 : C::ROW;
-    }
+    });
     const int clast = kPacked ? (int)nch - 1 : 0;
     // Scale load i of piece p of a scale group, likewise (packed: 256 bytes of a row group's run).
     const uint8_t *sbase[C::GS][C::SL];
     uint32_t srow[C::GS][C::SL];
     int scol[C::GS][C::SL], sstep[C::GS][C::SL], send[C::GS][C::SL];
-#pragma unroll
-    for (int p = 0; p < C::GS; ++p)
-#pragma unroll
-        for (int i = 0; i < C::SL; ++i) {
+    static_for<0, C::GS>([&](auto PP) __attribute__((always_inline)) {
+        static_for<0, C::SL>([&](auto I) __attribute__((always_inline)) {
+            constexpr int p = decltype(PP)::value, i = decltype(I)::value;
             const int w = wave * C::SL + i, j = p * C::SPP + (w < C::SPP ? w : C::SPP - 1);
             const bool a = j * C::SRPI < C::TM, pk = kPacked && !a;
             const int jb = j - C::TM / C::SRPI, row = j * C::SRPI + lane / C::SD;
@@ -187,11 +188,12 @@ __global__ __launch_bounds__(C::THREADS, C::LDS <= 80 * 1024 ? C::WAVES / 2 : C:
             scol[p][i] = pk ? jb * 256 % C::RUN + lane * 4 : ((lane % C::SD) ^ C::fs(row)) * 4;
             sstep[p][i] = pk ? C::RUN : C::SROW;
             send[p][i] = per - 4;
-        }
+        });
+    });
     // Scale load i of piece p of scale group g (past the last group: of the last, into
     // a buffer nobody reads).  Columns past K re-read the row's last ones, here and
     // below: they belong to slices that are skipped.
-    auto load_scale = [&](int g, int p, int i) {
+    auto load_scale = [&](int g, int p, int i) __attribute__((always_inline)) {
         const int w = wave * C::SL + i, j = p * C::SPP + (w < C::SPP ? w : C::SPP - 1);
         const int step = sstep[p][i], at = (g < ngrp ? g : ngrp - 1) * step;
         const int left = send[p][i] - at, lim = left < step ? left : step;
@@ -200,7 +202,7 @@ __global__ __launch_bounds__(C::THREADS, C::LDS <= 80 * 1024 ? C::WAVES / 2 : C:
     };
     // Load L of this wave's share of stage s (of parity PAR): its piece of a scale
     // group, then the code loads.
-    auto load_one = [&](int s, int buf, auto LL, auto PAR) {
+    auto load_one = [&](int s, int buf, auto LL, auto PAR) __attribute__((always_inline)) {
         constexpr int L = decltype(LL)::value;
         if constexpr (L < C::SL) {
             load_scale(C::GS == 1 ? s : s / C::GS + 1, C::GS == 1 ? 0 : decltype(PAR)::value, L);
@@ -269,10 +271,11 @@ __global__ __launch_bounds__(C::THREADS, C::LDS <= 80 * 1024 ? C::WAVES / 2 : C:
     using I0 = std::integral_constant<int, 0>;
 
     // prologue: scale group 0 and stages 0 .. NBUF-1 on their way, slice 0 in registers
-#pragma unroll
-    for (int p = 0; p < (C::GS > 1 ? C::GS : 0); ++p)
-#pragma unroll
-        for (int i = 0; i < C::SL; ++i) load_scale(0, p, i);
+    static_for<0, (C::GS > 1 ? C::GS : 0)>([&](auto PP) __attribute__((always_inline)) {
+        static_for<0, C::SL>([&](auto I) __attribute__((always_inline)) {
+            load_scale(0, decltype(PP)::value, decltype(I)::value);
+        });
+    });
     static_for<0, NBUF>([&](auto S) {
         constexpr int s = decltype(S)::value;
         if (s < nst) load_all(s, s, std::integral_constant<int, s & 1>{});

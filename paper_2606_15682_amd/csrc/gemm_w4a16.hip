@@ -18,6 +18,10 @@
 // 1024 in total; at most 12 splits) whose FP32 partial sums a second kernel
 // adds in split order (deterministic).
 //
+// Up to 16 rows of x and a short W, gemm_w4a16_decode_kernel keeps K inside a
+// workgroup instead; from 33 rows on the tiles of gemm_w4a16_tile.hip take
+// over where they promise less time.
+//
 // The weights come row-major (codes [N][K/2], scales [N][K/32]) or as the
 // packed image of w4a16_pack_kernel: per 16-row group and 128-element chunk,
 // the 1 KB of codes in the order the lanes below load them, then (after all

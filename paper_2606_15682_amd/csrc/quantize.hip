@@ -23,8 +23,10 @@
 //     more than the 2^-16 snap, so the side of every midpoint is kept.  The
 //     path is taken only when s g is in [2^-123, 2^125], so subnormal inputs
 //     (which round to code 0 either way) cannot disturb it.
-//   * general path (NaN/Inf blocks, all-zero NVFP4 blocks, a non-power-of-two
-//     global scale, extreme exponents): integer thresholds on the bfloat16
+//   * NVFP4 codes under a g that is not a power of two: FP32 quotients and the
+//     sign of an exact residual (emit_codes_any_g).
+//   * general path (NaN/Inf blocks, all-zero NVFP4 blocks, other outputs under a
+//     non-power-of-two global scale, extreme exponents): integer thresholds on the bfloat16
 //     magnitude pattern (see fp4_device.h).
 // Fake-quant decodes the codes again with v_cvt_scalef32_pk_{bf16,f32}_fp4
 // (code * 2^e, exact) and, for NVFP4, multiplies by m (exact, <= 6 bits).

@@ -434,9 +434,29 @@ __device__ __forceinline__ float local_global_scale(const uint16_t *__restrict__
         return *reinterpret_cast<const uint4 *>(x + (int64_t)r * ldx + (int64_t)(i - r * vpr) * 8);
     };
     // 16 loads in flight per thread: a tensor of up to 16 * THREADS vectors
-    // (32K elements, a decode step's activations) costs one memory round trip
+    // (32K elements, a decode step's activations) costs one memory round trip.
+    // Dense rows: no division per vector, and the packed maximum of all magnitudes; a
+    // thread whose maximum is not finite walks its vectors again below.
     uint32_t m = 0;
-    for (uint32_t i = threadIdx.x; i < nvec; i += INFLIGHT * THREADS) {
+    bool walk = true;
+    if (ldx == cols) {
+        const uint4 *v = reinterpret_cast<const uint4 *>(x);
+        us2 m2 = us2{0, 0};
+        for (uint32_t i = threadIdx.x; i < nvec; i += INFLIGHT * THREADS) {
+            uint4 d[INFLIGHT];
+#pragma unroll
+            for (int u = 0; u < INFLIGHT; ++u) {
+                const uint32_t j = i + u * THREADS;
+                d[u] = v[j < nvec ? j : nvec - 1];
+            }
+#pragma unroll
+            for (int u = 0; u < INFLIGHT; ++u) m2 = mag_max8(d[u], m2);
+        }
+        m = m2[0] > m2[1] ? m2[0] : m2[1];
+        walk = m >= 0x7F80u;
+        if (walk) m = 0;
+    }
+    for (uint32_t i = threadIdx.x; walk && i < nvec; i += INFLIGHT * THREADS) {
         uint4 d[INFLIGHT];
 #pragma unroll
         for (int u = 0; u < INFLIGHT; ++u) d[u] = vec(i + u * THREADS);

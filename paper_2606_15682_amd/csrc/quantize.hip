@@ -32,7 +32,7 @@
 // (code * 2^e, exact) and, for NVFP4, multiplies by m (exact, <= 6 bits).
 //
 // NVFP4 computed global scale, by tensor size:
-//   up to 2^16 elements: one launch; each workgroup reads the whole tensor for
+//   up to 3 * 2^16 elements: one launch; each workgroup reads the whole tensor for
 //     its amax before its block loop (kGLocal);
 //   up to 2^19 segments of 64 blocks: one pass over x under per-segment
 //     reference scales, then a fix-up kernel (kGDeferred, nv_fixup_kernel);

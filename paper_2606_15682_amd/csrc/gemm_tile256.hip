@@ -54,6 +54,7 @@
 #include <type_traits>
 
 #include "fp4_device.h"
+#include "g2l.h"
 #include "internal.h"
 
 // MXFP4 stages: with scale groups (K % 512 == 0), K = 256 per stage in two
@@ -89,18 +90,10 @@ typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef _Float16 v2h __attribute__((ext_vector_type(2)));
-typedef __attribute__((address_space(3))) void lds_void;
 
 constexpr int kThreads = 256;
 constexpr int TM = 256, TN = 256;
 
-// Calls f(integral_constant<int, J>) for J = B .. E-1, unrolled at compile time.
-template <int B, int E, typename F> __device__ __forceinline__ void static_for(F &&f) {
-    if constexpr (B < E) {
-        f(std::integral_constant<int, B>{});
-        static_for<B + 1, E>(f);
-    }
-}
 constexpr int GROUP_M = 8;
 
 // GS (MXFP4 with K % 512 == 0 and 16-byte aligned scales): the scale bytes
@@ -140,19 +133,6 @@ struct Cfg {
     static_assert(!GS || (FMT == kMX && GROW == 16 && GLPW == 2 && GSTAGES >= 2),
                   "scale groups: 16 bytes per row, 2 loads per wave");
 };
-
-// Direct-to-LDS loads: lane i's 16 (4) bytes at base + voff land at LDS
-// address l + 16 i (4 i); base and l are wave-uniform.  Written as inline asm
-// so the compiler does not track them: it would otherwise wait for every
-// such load in flight (vmcnt(0)) before any later LDS read, since it cannot
-// tell which stage buffer a read touches.  The kernels order these writes
-// against their LDS reads themselves (vmcnt waits and barriers).
-__device__ __forceinline__ void g2l16(const uint8_t *base, uint32_t voff, uint8_t *l) {
-    asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "{m0}"((uint32_t)(uintptr_t)l));
-}
-__device__ __forceinline__ void g2l4(const uint8_t *base, uint32_t voff, uint8_t *l) {
-    asm volatile("global_load_lds_dword %0, %1" ::"v"(voff), "s"(base), "{m0}"((uint32_t)(uintptr_t)l));
-}
 
 // A float read through the scalar cache (the pointer is uniform).
 __device__ __forceinline__ float uniform_load(const float *p) {

@@ -37,6 +37,7 @@
 #include <type_traits>
 
 #include "fp4_device.h"
+#include "g2l.h"
 #include "internal.h"
 
 namespace reqat {
@@ -67,14 +68,6 @@ typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 256;          // four waves
 constexpr int kMaxSplits = REQAT_W16_KSMAX;
-
-// Calls f(integral_constant<int, J>) for J = B .. E-1, unrolled at compile time.
-template <int B, int E, typename F> __device__ __forceinline__ void static_for(F &&f) {
-    if constexpr (B < E) {
-        f(std::integral_constant<int, B>{});
-        static_for<B + 1, E>(f);
-    }
-}
 
 __device__ __forceinline__ uint32_t pick4(const v4u &q, int s) {
     return s == 0 ? q.x : s == 1 ? q.y : s == 2 ? q.z : q.w;

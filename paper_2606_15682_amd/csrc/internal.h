@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "dispatch.h"
+
 namespace reqat {
 
 // Maximum number of partial maxima the absmax pass produces; the workspace
@@ -16,16 +18,6 @@ constexpr int kMaxPartials = REQAT_MAX_PARTIALS;
 
 // Segment-table capacity of the quantize workspace (segments of 64 blocks).
 constexpr int64_t kMaxSegments = int64_t(1) << 19;
-
-// Tensors of at most this many elements are small enough for every workgroup
-// to read whole (<= 384 KB, from L2): their NVFP4 global scale is computed in one
-// launch (kGLocal).  One launch / pass and fix-up, us in a graph: 16 x 1536 3.1 / -,
-// 64 x 1536 4.4 / 6.5, 16 x 8960 5.6 / 6.7, 10 x 18944 6.2 / 6.7; it grows by 0.6 to 0.3 us per
-// 2^15 elements, the two launches hardly, so the line lies here.
-constexpr int64_t kLocalMaxElems = int64_t(3) << 16;
-
-// Format selector shared by the launchers (same values as the C ABI enum).
-enum Fmt : int { kNV = 0, kMX = 1 };
 
 // Output selector for the block quantizer.
 // kBoth writes codes, scales and fake-quant values in one pass over x.

@@ -32,8 +32,8 @@
 // (code * 2^e, exact) and, for NVFP4, multiplies by m (exact, <= 6 bits).
 //
 // NVFP4 computed global scale, by tensor size:
-//   up to 3 * 2^16 elements: one launch; each workgroup reads the whole tensor for
-//     its amax before its block loop (kGLocal);
+//   up to 3 * 2^16 elements (2^16 where rows have a stride): one launch; each
+//     workgroup reads the whole tensor for its amax before its block loop (kGLocal);
 //   up to 2^19 segments of 64 blocks: one pass over x under per-segment
 //     reference scales, then a fix-up kernel (kGDeferred, nv_fixup_kernel);
 //   beyond: a first pass writes one partial absmax per workgroup into the
@@ -812,7 +812,7 @@ hipError_t launch_quantize(Fmt fmt, QuantOut out, const uint16_t *x, int64_t row
     if (total == 0) return hipSuccess;
     const int64_t nseg = (total + kSeg - 1) / kSeg;
     const bool nv = fmt == kNV;
-    const bool local = nv && gsrc == kGComputed && total * B <= kLocalMaxElems;
+    const bool local = nv && gsrc == kGComputed && nv_one_launch(total * B, ldx == cols);
     const bool deferred = !local && nv && gsrc == kGComputed && seg_table != nullptr && nseg <= seg_capacity;
     int nparts = 0;
     if (nv && gsrc == kGComputed && !deferred && !local) {
@@ -823,7 +823,7 @@ hipError_t launch_quantize(Fmt fmt, QuantOut out, const uint16_t *x, int64_t row
     int64_t grid = (nseg + 4 * kSegPerWave - 1) / (4 * kSegPerWave);
     if (grid > kMaxGroups) grid = kMaxGroups;
     if (grid < 1) grid = 1;
-    // small tensor: one segment per wave (at most 16 workgroups, each reading
+    // small tensor: one segment per wave (at most 48 workgroups, each reading
     // all of x for the amax) keeps each wave's chain of block arithmetic short
     if (local) grid = (nseg + 3) / 4;
     // one pass with a computed g writing fake-quant values (two segments per

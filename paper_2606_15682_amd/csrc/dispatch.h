@@ -23,4 +23,218 @@ inline bool nv_one_launch(int64_t elems, bool dense) {
     return elems <= (dense ? kLocalMaxElems : kLocalMaxElemsStrided);
 }
 
+// ---------------------------------------------------------------- W4A4 product
+
+// Tiles of gemm_ksplit.hip.  The deep ones have twice the waves and a longer ring (128 x 128:
+// MXFP4 alone).  The last four serve up to 64 rows and take the packed decode image too.
+enum KsplitTile : int {
+    kTile64x64, kTile64x128, kTile128x128, kTile64x128Deep, kTile128x128Deep,
+    kTile32x32, kTile32x128, kTile64x32, kTile64x64Few
+};
+constexpr int kTileLarge = 5;                   // of pick_product_tile: 256 x 256 tiles (gemm_tile256.hip)
+constexpr int64_t kKsplitMaxK = int64_t(1) << 26;
+
+// Which kernel runs a product of M > 64 rows: the one with the least estimated
+// time, c + rounds (e + t K) with rounds = tiles / 256 CUs, rounded up, and a
+// time per K that one round alone does not fall below (too few waves per CU
+// to keep the matrix cores or the loads busy).  The numbers (nanoseconds; t per
+// element of K) are a fit to measurements over M = 65 .. 2048 and (N, K) =
+// (4608, 3584), (3584, 18944), (37888, 3584), (17920, 1536), (5120, 1280),
+// (1792, 5120), (5120, 3456), (7168, 5120), one HIP graph, weights from HBM.
+// Where it picks another kernel than the fastest, the two lay within 12% of
+// each other.  For example, in us, for 64 x 64 / 64 x 128 / 128 x 128 / 256 x 256:
+//   NVFP4  256 x 3584 x 18944: 45 / 85 / 131 / 331     1024 x 37888 x 3584: 386 / 277 / 259 / 237
+//   MXFP4  128 x 4608 x 3584: 8.2 / 12.7 / 15.4 / 28   777 x 7168 x 5120: 46 / 41 / 29 / 40
+//          2048 x 4608 x 3584: 55 / 38 / 35 / 29
+// The rule uses sizes alone, so a shape always runs the same kernel.
+//
+// The deep tiles (eight waves, one workgroup per CU, three or four stages on their
+// way) are for a single round: alone on a CU the plain 64 x 128 and 128 x 128 tiles
+// wait a microsecond for each stage of 256 elements, shared by two workgroups they
+// do not.  Plain / deep, in us: MXFP4 777 x 3584 x 18944 75 / 47, 777 x 1792 x 5120 16.5 / 12.9,
+// NVFP4 256 x 5120 x 13824 63 / 52; in two rounds 1536 x 5120 x 1280 (MXFP4) 13.6 / 15.4.
+struct ProductCost {
+    int tm, tn;
+    bool single;                                // for one round alone
+    double c, e, t, alone;
+};
+constexpr ProductCost kProductCost[2][6] = {              // by KsplitTile, then 256 x 256
+    // NVFP4
+    {{64, 64, false, 3000, 1800, 2.15, 0}, {64, 128, false, 4000, 0, 3.6, 4.2}, {128, 128, false, 4000, 0, 6.9, 7.6},
+     {64, 128, true, 4500, 0, 3.6, 0}, {0, 0, true, 0, 0, 0, 0}, {256, 256, false, 4000, 0, 22, 20}},
+    // MXFP4
+    {{64, 64, false, 3000, 1200, 1.3, 0}, {64, 128, false, 3000, 700, 2.0, 3.4}, {128, 128, false, 3000, 700, 2.9, 4.0},
+     {64, 128, true, 3500, 0, 2.4, 0}, {128, 128, true, 4000, 0, 2.7, 0}, {256, 256, false, 3000, 700, 7.7, 0}},
+};
+
+// Small tiles have to promise this much: where the estimates are closer they
+// err, mostly for many rounds of long rows (3855 x 5120 x 27648, five rounds of 128 x 128
+// against two: 4% under the 256 x 256 tiles by the estimate, 4% over them measured).
+constexpr double kLargeBias = 0.88;
+
+// The KsplitTile, or kTileLarge: 256 x 256 tiles
+inline int pick_product_tile(Fmt fmt, int64_t M, int64_t N, int64_t K, bool big_ok) {
+    int best = 0;
+    double least = 0;
+    for (int i = 0; i < (big_ok ? kTileLarge + 1 : kTileLarge); ++i) {
+        const ProductCost &q = kProductCost[fmt == kMX][i];
+        if (q.tm == 0) continue;
+        const int64_t tiles = ((M + q.tm - 1) / q.tm) * ((N + q.tn - 1) / q.tn);
+        const double rounds = (double)((tiles + 255) / 256);
+        if (q.single && rounds > 1) continue;
+        const double t = rounds == 1 && q.alone > 0 ? q.alone : q.t;
+        const double est = q.c + rounds * (q.e + t * (double)K);
+        if (i == 0 || (i == kTileLarge ? kLargeBias : 1.0) * est < least) {
+            best = i;
+            least = est;
+        }
+    }
+    return best;
+}
+
+// 17 to 64 rows: the skinny kernel (16 rows of W per workgroup, which reads all of
+// X from L2 in 16-byte pieces: rounds of 256 workgroups, a time per K that grows
+// with the tiles of 16 rows of X), or a tile that takes X through LDS once for 32 to
+// 128 rows of W.  Up to 16 rows the skinny kernel is the faster one nearly
+// everywhere.  Same form of estimate, fitted over the same weights from HBM and
+// M = 17, 32, 48, 64.  For example, in us, skinny / the pick:
+//   MXFP4  64 x 27648 x 5120: 67 / 25    64 x 5120 x 13824: 39 / 19    64 x 2048 x 1536: 4.8 / 4.8 (skinny; 64 x 32: 6.0)
+//   NVFP4  64 x 27648 x 5120: 79 / 33    32 x 7168 x 5120: 12.1 / 10   64 x 1792 x 5120: 12.1 / 12.1 (skinny; 64 x 32: 13)
+struct DecodeCost {
+    int tm, tn;                                 // tn = 16: the skinny kernel
+    double c, t;
+};
+constexpr DecodeCost kDecode[2][7] = {
+    // NVFP4: skinny of two, three, four row tiles; 32 x 32, 32 x 128; 64 x 32, 64 x 64
+    {{32, 16, 2800, 0.93}, {48, 16, 2800, 1.3}, {64, 16, 2800, 1.8},
+     {32, 32, 4200, 1.15}, {32, 128, 4500, 3.8}, {64, 32, 4000, 1.5}, {64, 64, 4000, 2.7}},
+    // MXFP4
+    {{32, 16, 2000, 0.85}, {48, 16, 2400, 1.17}, {64, 16, 3000, 1.4},
+     {32, 32, 3000, 1.0}, {32, 128, 3800, 2.4}, {64, 32, 3200, 1.15}, {64, 64, 3500, 1.8}},
+};
+
+// -1: the skinny kernel; else the KsplitTile.  Sizes alone, so that packed and
+// row-major weights of a shape give the same result.
+inline int pick_decode_tile(Fmt fmt, int64_t M, int64_t N, int64_t K) {
+    if (M <= 16 || K > kKsplitMaxK) return -1;
+    constexpr int kTile[7] = {-1, -1, -1, kTile32x32, kTile32x128, kTile64x32, kTile64x64Few};
+    int best = -1;
+    double least = 0;
+    bool skinny = true;                         // the first skinny entry that holds M counts
+    for (int i = 0; i < 7; ++i) {
+        const DecodeCost &q = kDecode[fmt == kMX][i];
+        if (q.tn == 16 ? !skinny || M > q.tm : q.tm != (M <= 32 ? 32 : 64)) continue;
+        if (q.tn == 16) skinny = false;
+        const int64_t tiles = (N + q.tn - 1) / q.tn;
+        const double est = q.c + (double)((tiles + 255) / 256) * q.t * (double)K;
+        if (q.tn == 16 || est < least) {
+            best = kTile[i];
+            least = est;
+        }
+    }
+    return best;
+}
+
+// ---------------------------------------------------------------- W4A16 product
+
+#ifndef REQAT_W16_NT
+#define REQAT_W16_NT 1
+#endif
+#ifndef REQAT_W16_KSMAX
+#define REQAT_W16_KSMAX 12
+#endif
+#ifndef REQAT_W16_TARGET
+#define REQAT_W16_TARGET 1024
+#endif
+
+// Tiles of gemm_w4a16_tile.hip (M > 32), and the two kernels of gemm_w4a16.hip.
+enum W16Tile : int {
+    kW16Decode = -2, kW16Split = -1, kW16Tile64x64, kW16Tile64x128, kW16Tile128x128, kW16Tile128x128x8
+};
+constexpr int64_t kW16TileMaxLd = int64_t(1) << 23;
+
+inline int w4a16_row_tile(int64_t M) { return M <= 16 ? 1 : (M <= 32 ? 2 : 4); }
+
+// K splits, when the weight rows alone give fewer workgroups than CUs: the
+// fewest splits (fewest FP32 partials to add) that give about two workgroups
+// per CU, spread evenly (the average CU has at least 90% of the busiest CU's
+// count, so no CU runs a round alone); when no split count up to
+// REQAT_W16_KSMAX does, enough to reach REQAT_W16_TARGET workgroups.  At most
+// REQAT_W16_KSMAX splits and one pair of chunks each (splits start at even
+// chunks).  On 16 x 5120 x 27648 (80 row groups) the first rule picks 6:
+// 20.3 us against 21.6 for 12 and 24.5 for 4, which leaves a quarter of the
+// CUs with one workgroup more than the rest.  The split depends on the shape
+// alone, never on the device, so results are deterministic.
+inline int gemm_w4a16_splits(int64_t M, int64_t N, int64_t K) {
+    constexpr int64_t kCUs = 256;
+    const int64_t rows = 64 * REQAT_W16_NT;
+    const int64_t base = ((N + rows - 1) / rows) * ((M + 16 * w4a16_row_tile(M) - 1) / (16 * w4a16_row_tile(M)));
+    const int64_t npair = K / 256;
+    if (base >= kCUs || npair <= 1) return 1;
+    const int64_t kmax = REQAT_W16_KSMAX < npair ? REQAT_W16_KSMAX : npair;
+    for (int64_t ks = 2; ks <= kmax; ++ks) {
+        const int64_t wg = base * ks, busiest = (wg + kCUs - 1) / kCUs;
+        if (10 * wg >= 18 * kCUs && 10 * wg >= 9 * busiest * kCUs) return (int)ks;
+    }
+    int64_t ks = (REQAT_W16_TARGET + base - 1) / base;
+    return (int)(ks < kmax ? ks : kmax);
+}
+
+// From 33 rows on: gemm_w4a16_kernel (64 rows of x and of W per workgroup, K split over
+// workgroups) or the tile with the least estimated time, where it promises 12% or more.
+// That kernel: 9 us and 16 ns per 64 x 64 block and 1000 elements of K.  Tiles: c + rounds
+// t K; a workgroup alone on its CU and two sharing one finish at the same rate per tile,
+// so rounds = tiles / 256, half way to the next whole number.  Fitted over M = 64 .. 1024 and
+// twelve (N, K) from (2048, 1536) to (55296, 5120), weights from HBM.  For example, in us,
+// that kernel / 64 x 64 / 64 x 128 / 128 x 128 of 4 waves / of 8 waves:
+//   512 x 27648 x 5120: 221 / 181 / 131 / 130 / 142    512 x 5120 x 13824: 121 / 103 / 85 / 93 / 73
+//   64 x 5120 x 13824: 26 / 44 / 52 / 91 / 63          128 x 2048 x 1536: 11.6 / 7.1 / 9.1 / 13.7 / 12.4
+// Sizes alone decide, so packed and row-major weights give the same result.
+struct W16Cost {
+    int tm, tn;
+    double c, t;                                // ns, ns per element of K and round
+};
+constexpr W16Cost kW16Cost[4] = {{64, 64, 3200, 2.9}, {64, 128, 3200, 3.7}, {128, 128, 4000, 6.5}, {128, 128, 4500, 5.3}};
+
+// M <= 16: whether gemm_w4a16_decode_kernel, which reads x once for 16 rows of W, is faster
+// than gemm_w4a16_kernel, which reads it once for 64 and splits K over workgroups where those
+// are fewer than the CUs.  Estimates in us, K in thousands, fitted over twenty (N, K) from
+// (768, 1536) to (55296, 5120) and M = 1, 4, 8, 16, weights from HBM; 5% has to be promised.
+// For example, split or unsplit / this one:
+//   4 x 3584 x 3584 7.1 / 4.1    4 x 55296 x 5120 34.9 / 32.9    16 x 2048 x 1536 6.0 / 3.5
+//   8 x 7168 x 5120 11.1 / 8.2   4 x 5120 x 27648 20.5 / 23.8    16 x 27648 x 5120 21 / 37
+inline bool w4a16_decode_pays(int64_t M, int64_t N, int64_t K) {
+    if (M > 16 || K <= 0) return false;
+    const double k = 1e-3 * (double)K, w = 1e-6 * (double)N * (double)K, wg = (double)((N + 15) / 16) / 256;
+    const double split = N <= 64 * 255 ? 5.6 + 0.11 * w : 3.2 + 0.112 * w;
+    const double rate = M <= 4 ? 0.39 : (M <= 8 ? 0.52 : 0.93);
+    const double rounds = wg <= 1 ? 0.6 + 0.4 * wg : (double)(((N + 15) / 16 + 255) / 256);
+    return 2.6 + rounds * rate * k < 0.95 * split;
+}
+
+// kW16Split: gemm_w4a16_kernel; else the tile.
+inline int pick_w4a16_tile(int64_t M, int64_t N, int64_t K, int64_t ldx) {
+    if (M <= 32 || K <= 0 || K > kW16TileMaxLd || ldx > kW16TileMaxLd) return kW16Split;
+    int best = kW16Split;
+    double least = 0.88 * (9000 + 0.016 * (double)((N + 63) / 64) * (double)((M + 63) / 64) * (double)K);
+    for (int i = 0; i < 4; ++i) {
+        const W16Cost &q = kW16Cost[i];
+        const int64_t tiles = ((M + q.tm - 1) / q.tm) * ((N + q.tn - 1) / q.tn);
+        if (i == kW16Tile128x128x8 && tiles > 256) continue;    // one workgroup per CU: for a single round
+        const double full = (double)tiles / 256, rounds = tiles <= 256 ? 1.0 : 0.5 * (full + (double)((tiles + 255) / 256));
+        const double est = q.c + rounds * q.t * (double)K;
+        if (est < least) {
+            best = i;
+            least = est;
+        }
+    }
+    return best;
+}
+
+// The W4A16 kernel of a product: a W16Tile.
+inline int pick_w4a16(int64_t M, int64_t N, int64_t K, int64_t ldx) {
+    const int tile = pick_w4a16_tile(M, N, K, ldx);
+    return tile < 0 && w4a16_decode_pays(M, N, K) ? kW16Decode : tile;
+}
+
 }  // namespace reqat

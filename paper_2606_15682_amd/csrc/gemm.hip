@@ -19,8 +19,8 @@
 // exact products in FP32.  One 32x32x16 step covers exactly one 16-element
 // NVFP4 block per row.  g_a * g_b is applied in the epilogue.
 //
-// This file holds the choice of kernel for a product and the general kernel,
-// which runs what the tiled ones do not take: K == 0 (it writes zeros) and, with
+// This file launches the kernel that dispatch.h chooses for a product, and holds the
+// general kernel, which runs what the tiled ones do not take: K == 0 (it writes zeros) and, with
 // M > 64, rows of more than kKsplitMaxK elements.  Tiling: 128 x 128 output tile per 256-thread workgroup, 2 x 2 waves of 64 x 64 (2 x 2
 // MFMA tiles of 32 x 32), K staged 128 elements at a time through LDS.
 #include "fp4_device.h"
@@ -193,117 +193,11 @@ __global__ __launch_bounds__(kThreads) void gemm_w4a4_kernel(
 
 }  // namespace
 
-namespace {
-
-// Which kernel runs a product of M > 64 rows: the one with the least estimated
-// time, c + rounds (e + t K) with rounds = tiles / 256 CUs, rounded up, and a
-// time per K that one round alone does not fall below (too few waves per CU
-// to keep the matrix cores or the loads busy).  The numbers (nanoseconds; t per
-// element of K) are a fit to measurements over M = 65 .. 2048 and (N, K) =
-// (4608, 3584), (3584, 18944), (37888, 3584), (17920, 1536), (5120, 1280),
-// (1792, 5120), (5120, 3456), (7168, 5120), one HIP graph, weights from HBM.
-// Where it picks another kernel than the fastest, the two lay within 12% of
-// each other.  For example, in us, for 64 x 64 / 64 x 128 / 128 x 128 / 256 x 256:
-//   NVFP4  256 x 3584 x 18944: 45 / 85 / 131 / 331     1024 x 37888 x 3584: 386 / 277 / 259 / 237
-//   MXFP4  128 x 4608 x 3584: 8.2 / 12.7 / 15.4 / 28   777 x 7168 x 5120: 46 / 41 / 29 / 40
-//          2048 x 4608 x 3584: 55 / 38 / 35 / 29
-// The rule uses sizes alone, so a shape always runs the same kernel.
-//
-// The deep tiles (eight waves, one workgroup per CU, three or four stages on their
-// way) are for a single round: alone on a CU the plain 64 x 128 and 128 x 128 tiles
-// wait a microsecond for each stage of 256 elements, shared by two workgroups they
-// do not.  Plain / deep, in us: MXFP4 777 x 3584 x 18944 75 / 47, 777 x 1792 x 5120 16.5 / 12.9,
-// NVFP4 256 x 5120 x 13824 63 / 52; in two rounds 1536 x 5120 x 1280 (MXFP4) 13.6 / 15.4.
-struct TileCost {
-    int tm, tn;
-    bool single;                                // for one round alone
-    double c, e, t, alone;
-};
-constexpr int kTileLarge = 5;
-constexpr TileCost kCost[2][6] = {              // by KsplitTile, then 256 x 256
-    // NVFP4
-    {{64, 64, false, 3000, 1800, 2.15, 0}, {64, 128, false, 4000, 0, 3.6, 4.2}, {128, 128, false, 4000, 0, 6.9, 7.6},
-     {64, 128, true, 4500, 0, 3.6, 0}, {0, 0, true, 0, 0, 0, 0}, {256, 256, false, 4000, 0, 22, 20}},
-    // MXFP4
-    {{64, 64, false, 3000, 1200, 1.3, 0}, {64, 128, false, 3000, 700, 2.0, 3.4}, {128, 128, false, 3000, 700, 2.9, 4.0},
-     {64, 128, true, 3500, 0, 2.4, 0}, {128, 128, true, 4000, 0, 2.7, 0}, {256, 256, false, 3000, 700, 7.7, 0}},
-};
-
-// Small tiles have to promise this much: where the estimates are closer they
-// err, mostly for many rounds of long rows (3855 x 5120 x 27648, five rounds of 128 x 128
-// against two: 4% under the 256 x 256 tiles by the estimate, 4% over them measured).
-constexpr double kLargeBias = 0.88;
-
-// The KsplitTile, or kTileLarge: 256 x 256 tiles
-int pick_tile(Fmt fmt, int64_t M, int64_t N, int64_t K, bool big_ok) {
-    int best = 0;
-    double least = 0;
-    for (int i = 0; i < (big_ok ? kTileLarge + 1 : kTileLarge); ++i) {
-        const TileCost &q = kCost[fmt == kMX][i];
-        if (q.tm == 0) continue;
-        const int64_t tiles = ((M + q.tm - 1) / q.tm) * ((N + q.tn - 1) / q.tn);
-        const double rounds = (double)((tiles + 255) / 256);
-        if (q.single && rounds > 1) continue;
-        const double t = rounds == 1 && q.alone > 0 ? q.alone : q.t;
-        const double est = q.c + rounds * (q.e + t * (double)K);
-        if (i == 0 || (i == kTileLarge ? kLargeBias : 1.0) * est < least) {
-            best = i;
-            least = est;
-        }
-    }
-    return best;
-}
-
-// 17 to 64 rows: the skinny kernel (16 rows of W per workgroup, which reads all of
-// X from L2 in 16-byte pieces: rounds of 256 workgroups, a time per K that grows
-// with the tiles of 16 rows of X), or a tile that takes X through LDS once for 32 to
-// 128 rows of W.  Up to 16 rows the skinny kernel is the faster one nearly
-// everywhere.  Same form of estimate, fitted over the same weights from HBM and
-// M = 17, 32, 48, 64.  For example, in us, skinny / the pick:
-//   MXFP4  64 x 27648 x 5120: 67 / 25    64 x 5120 x 13824: 39 / 19    64 x 2048 x 1536: 4.8 / 4.8 (skinny; 64 x 32: 6.0)
-//   NVFP4  64 x 27648 x 5120: 79 / 33    32 x 7168 x 5120: 12.1 / 10   64 x 1792 x 5120: 12.1 / 12.1 (skinny; 64 x 32: 13)
-struct DecodeCost {
-    int tm, tn;                                 // tn = 16: the skinny kernel
-    double c, t;
-};
-constexpr DecodeCost kDecode[2][7] = {
-    // NVFP4: skinny of two, three, four row tiles; 32 x 32, 32 x 128; 64 x 32, 64 x 64
-    {{32, 16, 2800, 0.93}, {48, 16, 2800, 1.3}, {64, 16, 2800, 1.8},
-     {32, 32, 4200, 1.15}, {32, 128, 4500, 3.8}, {64, 32, 4000, 1.5}, {64, 64, 4000, 2.7}},
-    // MXFP4
-    {{32, 16, 2000, 0.85}, {48, 16, 2400, 1.17}, {64, 16, 3000, 1.4},
-     {32, 32, 3000, 1.0}, {32, 128, 3800, 2.4}, {64, 32, 3200, 1.15}, {64, 64, 3500, 1.8}},
-};
-
-// -1: the skinny kernel; else the KsplitTile.  Sizes alone, so that packed and
-// row-major weights of a shape give the same result.
-int pick_decode(Fmt fmt, int64_t M, int64_t N, int64_t K) {
-    if (M <= 16 || K > kKsplitMaxK) return -1;
-    constexpr int kTile[7] = {-1, -1, -1, kTile32x32, kTile32x128, kTile64x32, kTile64x64Few};
-    int best = -1;
-    double least = 0;
-    bool skinny = true;                         // the first skinny entry that holds M counts
-    for (int i = 0; i < 7; ++i) {
-        const DecodeCost &q = kDecode[fmt == kMX][i];
-        if (q.tn == 16 ? !skinny || M > q.tm : q.tm != (M <= 32 ? 32 : 64)) continue;
-        if (q.tn == 16) skinny = false;
-        const int64_t tiles = (N + q.tn - 1) / q.tn;
-        const double est = q.c + (double)((tiles + 255) / 256) * q.t * (double)K;
-        if (q.tn == 16 || est < least) {
-            best = kTile[i];
-            least = est;
-        }
-    }
-    return best;
-}
-
-}  // namespace
-
 hipError_t launch_gemm_decode(Fmt fmt, int64_t M, int64_t N, int64_t K, const uint8_t *a_codes,
                               const uint8_t *a_scales, const float *ga, const uint8_t *b_codes,
                               const uint8_t *b_scales, const float *gb, void *y, bool y_bf16, int64_t ldy,
                               bool packed, hipStream_t stream) {
-    const int tile = pick_decode(fmt, M, N, K);
+    const int tile = pick_decode_tile(fmt, M, N, K);
     if (tile < 0)
         return launch_gemm_skinny(fmt, M, N, K, a_codes, a_scales, ga, b_codes, b_scales, gb, y, y_bf16, ldy, packed,
                                   stream);
@@ -320,7 +214,7 @@ hipError_t launch_gemm(Fmt fmt, int64_t M, int64_t N, int64_t K, const uint8_t *
         return launch_gemm_decode(fmt, M, N, K, a_codes, a_scales, ga, b_codes, b_scales, gb, y, y_bf16,
                                   ldy, false, stream);
     if (K > 0 && K <= kKsplitMaxK) {
-        const int tile = pick_tile(fmt, M, N, K, gemm_tile256_supported(fmt, M, N, K, ldy));
+        const int tile = pick_product_tile(fmt, M, N, K, gemm_tile256_supported(fmt, M, N, K, ldy));
         if (tile == kTileLarge)
             return launch_gemm_tile256(fmt, M, N, K, a_codes, a_scales, ga, b_codes, b_scales, gb, y,
                                        y_bf16, ldy, stream);

@@ -49,18 +49,9 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
-#ifndef REQAT_W16_NT
-#define REQAT_W16_NT 1
-#endif
-#ifndef REQAT_W16_KSMAX
-#define REQAT_W16_KSMAX 12
-#endif
 
 #ifndef REQAT_W16_DEPTH1
 #define REQAT_W16_DEPTH1 4
-#endif
-#ifndef REQAT_W16_TARGET
-#define REQAT_W16_TARGET 1024
 #endif
 #ifndef REQAT_W16_XG
 #define REQAT_W16_XG 2
@@ -404,8 +395,6 @@ hipError_t launch_decode(int64_t M, int64_t N, int64_t K, const uint16_t *x, int
     return hipGetLastError();
 }
 
-int row_tile(int64_t M) { return M <= 16 ? 1 : (M <= 32 ? 2 : 4); }
-
 // Packed weight image (one thread per 16 code bytes, and per scale dword):
 // unit (G, c) of 16-row group G and 128-element chunk c holds 1024 code bytes,
 // piece q (bytes 16q .. 16q+15 of the chunk) of row 16G + r at byte
@@ -447,106 +436,26 @@ hipError_t launch_w4a16_pack(const uint8_t *codes, const uint8_t *scales, int64_
     return hipGetLastError();
 }
 
-// K splits, when the weight rows alone give fewer workgroups than CUs: the
-// fewest splits (fewest FP32 partials to add) that give about two workgroups
-// per CU, spread evenly (the average CU has at least 90% of the busiest CU's
-// count, so no CU runs a round alone); when no split count up to
-// REQAT_W16_KSMAX does, enough to reach REQAT_W16_TARGET workgroups.  At most
-// REQAT_W16_KSMAX splits and one pair of chunks each (splits start at even
-// chunks).  On 16 x 5120 x 27648 (80 row groups) the first rule picks 6:
-// 20.3 us against 21.6 for 12 and 24.5 for 4, which leaves a quarter of the
-// CUs with one workgroup more than the rest.  The split depends on the shape
-// alone, never on the device, so results are deterministic.
-int gemm_w4a16_splits(int64_t M, int64_t N, int64_t K) {
-    constexpr int64_t kCUs = 256;
-    const int64_t rows = 64 * REQAT_W16_NT;
-    const int64_t base = ((N + rows - 1) / rows) * ((M + 16 * row_tile(M) - 1) / (16 * row_tile(M)));
-    const int64_t npair = K / 256;
-    if (base >= kCUs || npair <= 1) return 1;
-    const int64_t kmax = REQAT_W16_KSMAX < npair ? REQAT_W16_KSMAX : npair;
-    for (int64_t ks = 2; ks <= kmax; ++ks) {
-        const int64_t wg = base * ks, busiest = (wg + kCUs - 1) / kCUs;
-        if (10 * wg >= 18 * kCUs && 10 * wg >= 9 * busiest * kCUs) return (int)ks;
-    }
-    int64_t ks = (REQAT_W16_TARGET + base - 1) / base;
-    return (int)(ks < kmax ? ks : kmax);
-}
-
 size_t gemm_w4a16_workspace_bytes(int64_t M, int64_t N, int64_t K) {
     const int ks = gemm_w4a16_splits(M, N, K);
     return ks > 1 ? sizeof(float) * (size_t)ks * (size_t)M * (size_t)N : 0;
 }
 
-namespace {
-
-// From 33 rows on: this file's kernel (64 rows of x and of W per workgroup, K split over
-// workgroups) or the tile with the least estimated time, where it promises 12% or more.
-// This kernel: 9 us and 16 ns per 64 x 64 block and 1000 elements of K.  Tiles: c + rounds
-// t K; a workgroup alone on its CU and two sharing one finish at the same rate per tile,
-// so rounds = tiles / 256, half way to the next whole number.  Fitted over M = 64 .. 1024 and
-// twelve (N, K) from (2048, 1536) to (55296, 5120), weights from HBM.  For example, in us,
-// this kernel / 64 x 64 / 64 x 128 / 128 x 128 of 4 waves / of 8 waves:
-//   512 x 27648 x 5120: 221 / 181 / 131 / 130 / 142    512 x 5120 x 13824: 121 / 103 / 85 / 93 / 73
-//   64 x 5120 x 13824: 26 / 44 / 52 / 91 / 63          128 x 2048 x 1536: 11.6 / 7.1 / 9.1 / 13.7 / 12.4
-// Sizes alone decide, so packed and row-major weights give the same result.
-struct TileCost {
-    int tm, tn;
-    double c, t;                                // ns, ns per element of K and round
-};
-constexpr TileCost kCost[4] = {{64, 64, 3200, 2.9}, {64, 128, 3200, 3.7}, {128, 128, 4000, 6.5}, {128, 128, 4500, 5.3}};
-
-// M <= 16: whether gemm_w4a16_decode_kernel, which reads x once for 16 rows of W, is faster
-// than gemm_w4a16_kernel, which reads it once for 64 and splits K over workgroups where those
-// are fewer than the CUs.  Estimates in us, K in thousands, fitted over twenty (N, K) from
-// (768, 1536) to (55296, 5120) and M = 1, 4, 8, 16, weights from HBM; 5% has to be promised.
-// For example, split or unsplit / this one:
-//   4 x 3584 x 3584 7.1 / 4.1    4 x 55296 x 5120 34.9 / 32.9    16 x 2048 x 1536 6.0 / 3.5
-//   8 x 7168 x 5120 11.1 / 8.2   4 x 5120 x 27648 20.5 / 23.8    16 x 27648 x 5120 21 / 37
-bool decode_pays(int64_t M, int64_t N, int64_t K) {
-    if (M > 16 || K <= 0) return false;
-    const double k = 1e-3 * (double)K, w = 1e-6 * (double)N * (double)K, wg = (double)((N + 15) / 16) / 256;
-    const double split = N <= 64 * 255 ? 5.6 + 0.11 * w : 3.2 + 0.112 * w;
-    const double rate = M <= 4 ? 0.39 : (M <= 8 ? 0.52 : 0.93);
-    const double rounds = wg <= 1 ? 0.6 + 0.4 * wg : (double)(((N + 15) / 16 + 255) / 256);
-    return 2.6 + rounds * rate * k < 0.95 * split;
-}
-
-// -1: this file's kernel; else the W16Tile.
-int pick_tile(int64_t M, int64_t N, int64_t K, int64_t ldx) {
-    if (M <= 32 || K <= 0 || K > kW16TileMaxLd || ldx > kW16TileMaxLd) return -1;
-    int best = -1;
-    double least = 0.88 * (9000 + 0.016 * (double)((N + 63) / 64) * (double)((M + 63) / 64) * (double)K);
-    for (int i = 0; i < 4; ++i) {
-        const TileCost &q = kCost[i];
-        const int64_t tiles = ((M + q.tm - 1) / q.tm) * ((N + q.tn - 1) / q.tn);
-        if (i == kW16Tile128x128x8 && tiles > 256) continue;    // one workgroup per CU: for a single round
-        const double full = (double)tiles / 256, rounds = tiles <= 256 ? 1.0 : 0.5 * (full + (double)((tiles + 255) / 256));
-        const double est = q.c + rounds * q.t * (double)K;
-        if (est < least) {
-            best = i;
-            least = est;
-        }
-    }
-    return best;
-}
-
-}  // namespace
-
 hipError_t launch_gemm_w4a16(int64_t M, int64_t N, int64_t K, const uint16_t *x, int64_t ldx,
                              const uint8_t *w_codes, const uint8_t *w_scales, bool packed, void *y, bool y_bf16,
                              int64_t ldy, float *workspace, hipStream_t stream) {
     if (M == 0 || N == 0) return hipSuccess;
-    const int tile = pick_tile(M, N, K, ldx);
+    const int tile = pick_w4a16(M, N, K, ldx);
     if (tile >= 0)
         return launch_gemm_w4a16_tile((W16Tile)tile, M, N, K, x, ldx, w_codes, w_scales, packed, y, y_bf16, ldy,
                                       stream);
-    if (decode_pays(M, N, K)) {
+    if (tile == kW16Decode) {
         if (M <= 4) return launch_decode<1>(M, N, K, x, ldx, w_codes, w_scales, packed, y, y_bf16, ldy, stream);
         if (M <= 8) return launch_decode<2>(M, N, K, x, ldx, w_codes, w_scales, packed, y, y_bf16, ldy, stream);
         return launch_decode<4>(M, N, K, x, ldx, w_codes, w_scales, packed, y, y_bf16, ldy, stream);
     }
     const int ks = gemm_w4a16_splits(M, N, K);
-    switch (row_tile(M)) {
+    switch (w4a16_row_tile(M)) {
     case 1: return launch_mt<1>(M, N, K, x, ldx, w_codes, w_scales, packed, y, y_bf16, ldy, ks, workspace, stream);
     case 2: return launch_mt<2>(M, N, K, x, ldx, w_codes, w_scales, packed, y, y_bf16, ldy, ks, workspace, stream);
     default: return launch_mt<4>(M, N, K, x, ldx, w_codes, w_scales, packed, y, y_bf16, ldy, ks, workspace, stream);

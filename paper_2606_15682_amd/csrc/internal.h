@@ -45,16 +45,13 @@ hipError_t launch_quantize_rht(QuantOut out, const uint16_t *x, int64_t rows, in
 
 // W4A16: bfloat16 x [M][ldx] times MXFP4 weights [N][K/2] (+ scales [N][K/32]), K % 128 == 0.
 // `workspace` holds gemm_w4a16_workspace_bytes(M, N, K) bytes of split-K partial sums.
-int gemm_w4a16_splits(int64_t M, int64_t N, int64_t K);
 size_t gemm_w4a16_workspace_bytes(int64_t M, int64_t N, int64_t K);
-// packed: w_codes / w_scales are the code and scale parts of the packed image
-// that launch_w4a16_pack writes (w4a16_packed_bytes(N, K) bytes).
-// Tiles for larger M (gemm_w4a16_tile.hip): 0 < K <= kW16TileMaxLd, K % 128 == 0, ldx <= kW16TileMaxLd.
-enum W16Tile : int { kW16Tile64x64, kW16Tile64x128, kW16Tile128x128, kW16Tile128x128x8 };
-constexpr int64_t kW16TileMaxLd = int64_t(1) << 23;
+// Tiles (gemm_w4a16_tile.hip): 0 < K <= kW16TileMaxLd, K % 128 == 0, ldx <= kW16TileMaxLd; packed as below.
 hipError_t launch_gemm_w4a16_tile(W16Tile tile, int64_t M, int64_t N, int64_t K, const uint16_t *x, int64_t ldx,
                                   const uint8_t *w_codes, const uint8_t *w_scales, bool packed, void *y, bool y_bf16,
                                   int64_t ldy, hipStream_t stream);
+// packed: w_codes / w_scales are the code and scale parts of the packed image
+// that launch_w4a16_pack writes (w4a16_packed_bytes(N, K) bytes).
 hipError_t launch_gemm_w4a16(int64_t M, int64_t N, int64_t K, const uint16_t *x, int64_t ldx,
                              const uint8_t *w_codes, const uint8_t *w_scales, bool packed, void *y, bool y_bf16,
                              int64_t ldy, float *workspace, hipStream_t stream);
@@ -96,11 +93,7 @@ hipError_t launch_gemm_tile256(Fmt fmt, int64_t M, int64_t N, int64_t K, const u
                                const uint8_t *b_scales, const float *gb, void *y, bool y_bf16,
                                int64_t ldy, hipStream_t stream);
 
-// Small tiles (gemm_ksplit.hip): 0 < K <= kKsplitMaxK, K % 128 == 0.  The deep ones have twice the
-// waves and a longer ring (128 x 128: MXFP4 alone).  The last four serve up to 64 rows and take the
-// packed decode image too.
-enum KsplitTile : int { kTile64x64, kTile64x128, kTile128x128, kTile64x128Deep, kTile128x128Deep, kTile32x32, kTile32x128, kTile64x32, kTile64x64Few };
-constexpr int64_t kKsplitMaxK = int64_t(1) << 26;
+// Small tiles (gemm_ksplit.hip): 0 < K <= kKsplitMaxK, K % 128 == 0.
 hipError_t launch_gemm_ksplit(KsplitTile tile, Fmt fmt, int64_t M, int64_t N, int64_t K, const uint8_t *a_codes,
                               const uint8_t *a_scales, const float *ga, const uint8_t *b_codes,
                               const uint8_t *b_scales, const float *gb, void *y, bool y_bf16, int64_t ldy,

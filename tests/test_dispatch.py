@@ -14,6 +14,10 @@ SOURCE = """
 using namespace reqat;
 extern "C" {
 int nv_one_launch_(int64_t elems, int dense) { return nv_one_launch(elems, dense); }
+int product_(int fmt, int64_t M, int64_t N, int64_t K, int big_ok) { return pick_product_tile((Fmt)fmt, M, N, K, big_ok); }
+int decode_(int fmt, int64_t M, int64_t N, int64_t K) { return pick_decode_tile((Fmt)fmt, M, N, K); }
+int w4a16_(int64_t M, int64_t N, int64_t K, int64_t ldx) { return pick_w4a16(M, N, K, ldx); }
+int w4a16_splits_(int64_t M, int64_t N, int64_t K) { return gemm_w4a16_splits(M, N, K); }
 }
 """
 
@@ -24,7 +28,14 @@ def rules(tmp_path_factory):
     (d / "rules.cpp").write_text(SOURCE)
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", libbuild.CSRC,
                     str(d / "rules.cpp"), "-o", str(d / "rules.so")], check=True)
-    return ctypes.CDLL(os.path.join(str(d), "rules.so"))
+    lib = ctypes.CDLL(os.path.join(str(d), "rules.so"))
+    size = ctypes.c_int64
+    lib.nv_one_launch_.argtypes = [size, ctypes.c_int]
+    lib.product_.argtypes = [ctypes.c_int, size, size, size, ctypes.c_int]
+    lib.decode_.argtypes = [ctypes.c_int, size, size, size]
+    lib.w4a16_.argtypes = [size] * 4
+    lib.w4a16_splits_.argtypes = [size] * 3
+    return lib
 
 
 @pytest.mark.parametrize("elems,dense,strided", [(16, 1, 1), (1 << 16, 1, 1), ((1 << 16) + 16, 1, 0),
@@ -32,5 +43,5 @@ def rules(tmp_path_factory):
 def test_computed_nvfp4_scale(rules, elems, dense, strided):
     """One launch up to 3 * 2^16 elements, but only up to 2^16 where rows have a stride: the
     walk over such rows costs twice the two launches at the end of that range."""
-    ask = lambda d: rules.nv_one_launch_(ctypes.c_int64(elems), d)
+    ask = lambda d: rules.nv_one_launch_(elems, d)
     assert (ask(1), ask(0)) == (dense, strided)

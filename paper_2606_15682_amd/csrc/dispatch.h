@@ -198,18 +198,21 @@ constexpr W16Cost kW16Cost[4] = {{64, 64, 3200, 2.9}, {64, 128, 3200, 3.7}, {128
 
 // M <= 16: whether gemm_w4a16_decode_kernel, which reads x once for 16 rows of W, is faster
 // than gemm_w4a16_kernel, which reads it once for 64 and splits K over workgroups where those
-// are fewer than the CUs.  Estimates in us, K in thousands, fitted over twenty (N, K) from
-// (768, 1536) to (55296, 5120) and M = 1, 4, 8, 16, weights from HBM; 5% has to be promised.
-// For example, split or unsplit / this one:
-//   4 x 3584 x 3584 7.1 / 4.1    4 x 55296 x 5120 34.9 / 32.9    16 x 2048 x 1536 6.0 / 3.5
-//   8 x 7168 x 5120 11.1 / 8.2   4 x 5120 x 27648 20.5 / 23.8    16 x 27648 x 5120 21 / 37
+// are fewer than the CUs.  Estimates in us, K in thousands, 5% has to be promised: fitted over
+// 3500 shapes, (N, K) up to (56000, 27648), M = 1 .. 16, both layouts, weights from HBM.  Over
+// those the pick takes 0.74 of gemm_w4a16_kernel's time (geometric mean); it is more than 5%
+// over it in 1% of them (row-major weights with K > 10000, at most 26%).  The time per round
+// keeps many rounds of short rows off it (3 x 47888 x 768: 7.9 / 10.4).  For example, in us,
+// gemm_w4a16_kernel / this one, packed weights:
+//   4 x 3584 x 3584 7.1 / 3.9    4 x 37888 x 3584 17.3 / 15.3    16 x 1536 x 1536 5.8 / 3.3
+//   7 x 7168 x 5120 11.1 / 7.7   7 x 5120 x 13824 12.4 / 14.7    16 x 27648 x 5120 19 / 36
 inline bool w4a16_decode_pays(int64_t M, int64_t N, int64_t K) {
     if (M > 16 || K <= 0) return false;
     const double k = 1e-3 * (double)K, w = 1e-6 * (double)N * (double)K, wg = (double)((N + 15) / 16) / 256;
-    const double split = N <= 64 * 255 ? 5.6 + 0.11 * w : 3.2 + 0.112 * w;
-    const double rate = M <= 4 ? 0.39 : (M <= 8 ? 0.52 : 0.93);
+    const double split = N <= 64 * 255 ? 5.6 + 0.11 * w : 3.2 + 0.118 * w;
+    const double rate = M <= 4 ? 0.38 : (M <= 8 ? 0.5 : 0.85);
     const double rounds = wg <= 1 ? 0.6 + 0.4 * wg : (double)(((N + 15) / 16 + 255) / 256);
-    return 2.6 + rounds * rate * k < 0.95 * split;
+    return 2.3 + rounds * (0.15 + rate * k) < 0.95 * split;
 }
 
 // kW16Split: gemm_w4a16_kernel; else the tile.

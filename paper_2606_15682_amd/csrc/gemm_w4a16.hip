@@ -253,10 +253,13 @@ __global__ __launch_bounds__(kThreads) void gemm_w4a16_kernel(
 }
 
 // Decode with few weight rows (M <= 16): a workgroup of eight waves owns 16 rows of W and
-// all of K, the waves taking contiguous shares of its chunks; their partial sums meet in
+// all of K, the waves taking its chunks in turn; their partial sums meet in
 // LDS and are added in the order of the waves.  Against K split over workgroups this
 // saves the partial sums' way through memory and the launch that adds them (4 us of 12 for
-// 4 x 7168 x 5120).  Each wave stages its own chunks of x in LDS, 4 RQ rows of 256 bytes in
+// 4 x 7168 x 5120).  In turn, because the waves then read whole lines of each weight row
+// side by side: with a contiguous share of K each, row-major weights took 5 to 13% longer
+// (packed ones up to 3%): 4 x 7168 x 5120 9.4 -> 8.9 us (packed 7.0 -> 6.8), 1 x 3584 x 18944
+// 14.2 -> 12.4 (9.3, 9.4), 7 x 5120 x 5120 10.5 -> 9.6 (7.5, 7.4).  Each wave stages its own chunks of x in LDS, 4 RQ rows of 256 bytes in
 // coalesced loads, and needs no barrier for them; 4 RQ >= M, rows past M re-read the
 // last one, and rows of D past 4 RQ come from row 4 RQ - 1 and are not stored.
 template <int RQ, bool kPacked>
@@ -272,7 +275,7 @@ __global__ __launch_bounds__(512) void gemm_w4a16_decode_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, kg = lane >> 4;
     const int64_t n0 = (int64_t)blockIdx.x * 16, nch = K / 128;
-    const int64_t c0 = nch * wave / kWaves, my = nch * (wave + 1) / kWaves - c0;
+    const int64_t my = (nch - wave + kWaves - 1) / kWaves;      // chunks wave, wave + kWaves, ...
 
     const uint16_t *xp[RQ];
 #pragma unroll
@@ -290,7 +293,7 @@ __global__ __launch_bounds__(512) void gemm_w4a16_decode_kernel(
     auto load = [&](int64_t i, auto J) {                // chunk i of the wave's
         constexpr int j = decltype(J)::value;
         if (i >= my) return;                            // uniform
-        const int64_t c = c0 + i;
+        const int64_t c = wave + kWaves * i;
         wv[j] = *reinterpret_cast<const v4u *>(wp + (kPacked ? c << 10 : c * 64));
         sv[j] = *reinterpret_cast<const uint32_t *>(sp + (kPacked ? c << 6 : c * 4));
 #pragma unroll

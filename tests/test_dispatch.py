@@ -45,3 +45,15 @@ def test_computed_nvfp4_scale(rules, elems, dense, strided):
     walk over such rows costs twice the two launches at the end of that range."""
     ask = lambda d: rules.nv_one_launch_(elems, d)
     assert (ask(1), ask(0)) == (dense, strided)
+
+
+W16_DECODE, W16_SPLIT = -2, -1
+
+
+@pytest.mark.parametrize("M,N,K,kernel", [
+    (4, 7168, 5120, W16_DECODE), (1, 37888, 3584, W16_DECODE), (4, 55296, 5120, W16_DECODE), (16, 1536, 1536, W16_DECODE),
+    (4, 5120, 27648, W16_SPLIT), (16, 27648, 5120, W16_SPLIT), (7, 5120, 13824, W16_SPLIT),
+    # many rounds of short rows, where the decode kernel took up to 1.4 times as long
+    (5, 40832, 512, W16_SPLIT), (1, 47216, 640, W16_SPLIT), (3, 47888, 768, W16_SPLIT), (7, 28608, 640, W16_SPLIT)])
+def test_w4a16_decode_kernel(rules, M, N, K, kernel):
+    assert rules.w4a16_(M, N, K, K) == kernel

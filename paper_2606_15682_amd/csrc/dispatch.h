@@ -92,45 +92,55 @@ inline int pick_product_tile(Fmt fmt, int64_t M, int64_t N, int64_t K, bool big_
     return best;
 }
 
-// 17 to 64 rows: the skinny kernel (16 rows of W per workgroup, which reads all of
-// X from L2 in 16-byte pieces: rounds of 256 workgroups, a time per K that grows
-// with the tiles of 16 rows of X), or a tile that takes X through LDS once for 32 to
-// 128 rows of W.  Up to 16 rows the skinny kernel is the faster one nearly
-// everywhere.  Same form of estimate, fitted over the same weights from HBM and
-// M = 17, 32, 48, 64.  For example, in us, skinny / the pick:
-//   MXFP4  64 x 27648 x 5120: 67 / 25    64 x 5120 x 13824: 39 / 19    64 x 2048 x 1536: 4.8 / 4.8 (skinny; 64 x 32: 6.0)
-//   NVFP4  64 x 27648 x 5120: 79 / 33    32 x 7168 x 5120: 12.1 / 10   64 x 1792 x 5120: 12.1 / 12.1 (skinny; 64 x 32: 13)
+// 17 to 64 rows: the skinny kernel (16 rows of W per workgroup, which reads all of X from L2
+// in 16-byte pieces, M rows of it), or a tile that takes X through LDS once for 32 to 128 rows
+// of W.  Up to 16 rows the skinny kernel is the faster one nearly everywhere.  The estimate, in
+// us with K in thousands:
+//   c + a K + rounds (e + b K + m K M / 64) + d K tiles / 256,   rounds = tiles / 256, rounded up:
+// workgroups beyond one per CU share its load path, so a round costs, and part of the time
+// goes with the tiles alone.  Fitted over 3500 shapes, N up to 56000, K up to 27648, both
+// layouts of W, from HBM; a tile has to promise 4%.  Over those shapes the pick takes 0.836 of
+// the skinny kernel's time (geometric mean) and 1.008 of the fastest one's; it is more than 5% over
+// the skinny kernel in 1% of them (at most 18%), where packed and row-major weights differ.
+// For example, in us, skinny / 64 x 32 / 64 x 64, packed weights:
+//   MXFP4  62 x 5120 x 5120 19.4 / 10.0 / 11.4    64 x 27648 x 5120 65 / 35 / 24    58 x 17 x 1152 3.6 / 5.4 / 5.5
+//   NVFP4  45 x 17776 x 640 9.5 / 15.8 / 9.1      54 x 2005 x 8576 14.9 / 17.1 / 25
 struct DecodeCost {
-    int tm, tn;                                 // tn = 16: the skinny kernel
-    double c, t;
+    int rows, tn, tile;                         // rows of X it serves; tile -1: the skinny kernel
+    double c, a, e, b, d, m;
 };
-constexpr DecodeCost kDecode[2][7] = {
-    // NVFP4: skinny of two, three, four row tiles; 32 x 32, 32 x 128; 64 x 32, 64 x 64
-    {{32, 16, 2800, 0.93}, {48, 16, 2800, 1.3}, {64, 16, 2800, 1.8},
-     {32, 32, 4200, 1.15}, {32, 128, 4500, 3.8}, {64, 32, 4000, 1.5}, {64, 64, 4000, 2.7}},
+constexpr DecodeCost kDecodeCost[2][7] = {
+    // NVFP4
+    {{32, 16, -1, 2.19, 0.28, 0.59, 0.16, 0.31, 0.69}, {48, 16, -1, 2.32, 0.40, 0.81, 0.20, 0.37, 0.63},
+     {64, 16, -1, 1.50, 0.15, 1.86, 0.46, 0.47, 0.76},
+     {32, 32, kTile32x32, 2.82, 0.25, 1.43, 0.63, 0.28, 0}, {32, 128, kTile32x128, 2.89, 1.11, 1.65, 1.86, 1.02, 0},
+     {64, 32, kTile64x32, 1.15, 0.13, 3.79, 1.13, 0.36, 0}, {64, 64, kTile64x64Few, 2.78, 0.63, 1.90, 1.65, 0.59, 0}},
     // MXFP4
-    {{32, 16, 2000, 0.85}, {48, 16, 2400, 1.17}, {64, 16, 3000, 1.4},
-     {32, 32, 3000, 1.0}, {32, 128, 3800, 2.4}, {64, 32, 3200, 1.15}, {64, 64, 3500, 1.8}},
+    {{32, 16, -1, 2.13, 0.16, 0.38, 0.09, 0.29, 0.75}, {48, 16, -1, 1.33, 0.13, 1.33, 0.20, 0.33, 0.76},
+     {64, 16, -1, 1.31, 0.10, 1.49, 0.18, 0.36, 0.85},
+     {32, 32, kTile32x32, 2.74, 0.21, 1.06, 0.21, 0.52, 0}, {32, 128, kTile32x128, 2.99, 0.48, 0.84, 0.87, 2.07, 0},
+     {64, 32, kTile64x32, 1.31, 0.17, 2.92, 0.44, 0.61, 0}, {64, 64, kTile64x64Few, 3.08, 0.21, 0.98, 0.70, 1.02, 0}},
 };
+constexpr double kSkinnyBias = 0.96;            // the promise
 
 // -1: the skinny kernel; else the KsplitTile.  Sizes alone, so that packed and
 // row-major weights of a shape give the same result.
 inline int pick_decode_tile(Fmt fmt, int64_t M, int64_t N, int64_t K) {
     if (M <= 16 || K > kKsplitMaxK) return -1;
-    constexpr int kTile[7] = {-1, -1, -1, kTile32x32, kTile32x128, kTile64x32, kTile64x64Few};
     int best = -1;
     double least = 0;
     bool skinny = true;                         // the first skinny entry that holds M counts
-    for (int i = 0; i < 7; ++i) {
-        const DecodeCost &q = kDecode[fmt == kMX][i];
-        if (q.tn == 16 ? !skinny || M > q.tm : q.tm != (M <= 32 ? 32 : 64)) continue;
-        if (q.tn == 16) skinny = false;
+    for (const DecodeCost &q : kDecodeCost[fmt == kMX]) {
+        if (q.tile < 0 ? !skinny || M > q.rows : q.rows != (M <= 32 ? 32 : 64)) continue;
         const int64_t tiles = (N + q.tn - 1) / q.tn;
-        const double est = q.c + (double)((tiles + 255) / 256) * q.t * (double)K;
-        if (q.tn == 16 || est < least) {
-            best = kTile[i];
+        const double k = 1e-3 * (double)K, rounds = (double)((tiles + 255) / 256), full = (double)tiles / 256;
+        const double est = (q.tile < 0 ? kSkinnyBias : 1.0) *
+                           (q.c + q.a * k + rounds * (q.e + q.b * k + q.m * k * (double)M / 64) + q.d * k * full);
+        if (q.tile < 0 || est < least) {
+            best = q.tile;
             least = est;
         }
+        if (q.tile < 0) skinny = false;
     }
     return best;
 }

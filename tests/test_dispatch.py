@@ -47,6 +47,21 @@ def test_computed_nvfp4_scale(rules, elems, dense, strided):
     assert (ask(1), ask(0)) == (dense, strided)
 
 
+NV, MX = 0, 1
+SKINNY, T32x32, T32x128, T64x32, T64x64F = -1, 5, 6, 7, 8
+
+
+@pytest.mark.parametrize("fmt,M,N,K,tile", [
+    (MX, 64, 7168, 5120, T64x32), (MX, 64, 27648, 5120, T64x64F), (NV, 32, 7168, 5120, T32x32), (NV, 24, 27648, 5120, T32x128),
+    (NV, 16, 27648, 5120, SKINNY), (MX, 16, 27648, 5120, SKINNY),
+    # where the first rule, rounds of tiles alone, lost up to 1.65 times to the skinny kernel
+    (NV, 39, 22560, 1664, T64x64F), (NV, 45, 17776, 640, SKINNY), (NV, 39, 17920, 1536, SKINNY),
+    (MX, 58, 17, 1152, SKINNY), (MX, 50, 304, 896, SKINNY), (MX, 53, 1504, 2432, SKINNY), (NV, 57, 20, 24960, SKINNY),
+    (NV, 19, 17024, 1280, T32x128)])
+def test_w4a4_decode_tile(rules, fmt, M, N, K, tile):
+    assert rules.decode_(fmt, M, N, K) == tile
+
+
 W16_DECODE, W16_SPLIT = -2, -1
 
 

@@ -23,6 +23,10 @@ inline bool nv_one_launch(int64_t elems, bool dense) {
     return elems <= (dense ? kLocalMaxElems : kLocalMaxElemsStrided);
 }
 
+// A launch holds fewer than 2^32 threads along x, and a tile has up to 512: where a kernel with one
+// workgroup per tile would need more of them, the rules below leave it out.
+constexpr int64_t kMaxTiles = (int64_t(1) << 23) - 1;
+
 // ---------------------------------------------------------------- W4A4 product
 
 // Tiles of gemm_ksplit.hip.  The deep ones have twice the waves and a longer ring (128 x 128:
@@ -72,19 +76,20 @@ constexpr ProductCost kProductCost[2][6] = {              // by KsplitTile, then
 // against two: 4% under the 256 x 256 tiles by the estimate, 4% over them measured).
 constexpr double kLargeBias = 0.88;
 
-// The KsplitTile, or kTileLarge: 256 x 256 tiles
+// The KsplitTile, or kTileLarge: 256 x 256 tiles; -1 (the general kernel) where neither can run
 inline int pick_product_tile(Fmt fmt, int64_t M, int64_t N, int64_t K, bool big_ok) {
-    int best = 0;
+    int best = -1;
     double least = 0;
     for (int i = 0; i < (big_ok ? kTileLarge + 1 : kTileLarge); ++i) {
         const ProductCost &q = kProductCost[fmt == kMX][i];
         if (q.tm == 0) continue;
         const int64_t tiles = ((M + q.tm - 1) / q.tm) * ((N + q.tn - 1) / q.tn);
+        if (i < kTileLarge && tiles > kMaxTiles) continue;
         const double rounds = (double)((tiles + 255) / 256);
         if (q.single && rounds > 1) continue;
         const double t = rounds == 1 && q.alone > 0 ? q.alone : q.t;
         const double est = q.c + rounds * (q.e + t * (double)K);
-        if (i == 0 || (i == kTileLarge ? kLargeBias : 1.0) * est < least) {
+        if (best < 0 || (i == kTileLarge ? kLargeBias : 1.0) * est < least) {
             best = i;
             least = est;
         }
@@ -133,6 +138,7 @@ inline int pick_decode_tile(Fmt fmt, int64_t M, int64_t N, int64_t K) {
     for (const DecodeCost &q : kDecodeCost[fmt == kMX]) {
         if (q.tile < 0 ? !skinny || M > q.rows : q.rows != (M <= 32 ? 32 : 64)) continue;
         const int64_t tiles = (N + q.tn - 1) / q.tn;
+        if (q.tile >= 0 && tiles > kMaxTiles) continue;
         const double k = 1e-3 * (double)K, rounds = (double)((tiles + 255) / 256), full = (double)tiles / 256;
         const double est = (q.tile < 0 ? kSkinnyBias : 1.0) *
                            (q.c + q.a * k + rounds * (q.e + q.b * k + q.m * k * (double)M / 64) + q.d * k * full);
@@ -217,7 +223,7 @@ constexpr W16Cost kW16Cost[4] = {{64, 64, 3200, 2.9}, {64, 128, 3200, 3.7}, {128
 //   4 x 3584 x 3584 7.1 / 3.9    4 x 37888 x 3584 17.3 / 15.3    16 x 1536 x 1536 5.8 / 3.3
 //   7 x 7168 x 5120 11.1 / 7.7   7 x 5120 x 13824 12.4 / 14.7    16 x 27648 x 5120 19 / 36
 inline bool w4a16_decode_pays(int64_t M, int64_t N, int64_t K) {
-    if (M > 16 || K <= 0) return false;
+    if (M > 16 || K <= 0 || (N + 15) / 16 > kMaxTiles) return false;
     const double k = 1e-3 * (double)K, w = 1e-6 * (double)N * (double)K, wg = (double)((N + 15) / 16) / 256;
     const double split = N <= 64 * 255 ? 5.6 + 0.11 * w : 3.2 + 0.118 * w;
     const double rate = M <= 4 ? 0.38 : (M <= 8 ? 0.5 : 0.85);
@@ -233,6 +239,7 @@ inline int pick_w4a16_tile(int64_t M, int64_t N, int64_t K, int64_t ldx) {
     for (int i = 0; i < 4; ++i) {
         const W16Cost &q = kW16Cost[i];
         const int64_t tiles = ((M + q.tm - 1) / q.tm) * ((N + q.tn - 1) / q.tn);
+        if (tiles > kMaxTiles) continue;
         if (i == kW16Tile128x128x8 && tiles > 256) continue;    // one workgroup per CU: for a single round
         const double full = (double)tiles / 256, rounds = tiles <= 256 ? 1.0 : 0.5 * (full + (double)((tiles + 255) / 256));
         const double est = q.c + rounds * q.t * (double)K;

@@ -21,8 +21,9 @@
 //
 // This file launches the kernel that dispatch.h chooses for a product, and holds the
 // general kernel, which runs what the tiled ones do not take: K == 0 (it writes zeros) and, with
-// M > 64, rows of more than kKsplitMaxK elements.  Tiling: 128 x 128 output tile per 256-thread workgroup, 2 x 2 waves of 64 x 64 (2 x 2
-// MFMA tiles of 32 x 32), K staged 128 elements at a time through LDS.
+// M > 64, rows of more than kKsplitMaxK elements and more than kMaxTiles tiles.  Its tiling: 128 x 128
+// output tile per 256-thread workgroup, 2 x 2 waves of 64 x 64 (2 x 2 MFMA tiles of 32 x 32), K staged
+// 128 elements at a time through LDS.
 #include "fp4_device.h"
 #include "internal.h"
 
@@ -218,10 +219,11 @@ hipError_t launch_gemm(Fmt fmt, int64_t M, int64_t N, int64_t K, const uint8_t *
         if (tile == kTileLarge)
             return launch_gemm_tile256(fmt, M, N, K, a_codes, a_scales, ga, b_codes, b_scales, gb, y,
                                        y_bf16, ldy, stream);
-        return launch_gemm_ksplit((KsplitTile)tile, fmt, M, N, K, a_codes, a_scales, ga, b_codes, b_scales, gb, y,
-                                  y_bf16, ldy, false, stream);
+        if (tile >= 0)
+            return launch_gemm_ksplit((KsplitTile)tile, fmt, M, N, K, a_codes, a_scales, ga, b_codes, b_scales, gb,
+                                      y, y_bf16, ldy, false, stream);
     }
-    // K == 0 (writes zeros), or rows beyond the 32-bit offsets of the tiled kernels
+    // K == 0 (writes zeros), rows beyond the 32-bit offsets of the tiled kernels, or more tiles than a launch holds
     dim3 grid((unsigned)((N + BN - 1) / BN), (unsigned)((M + BM - 1) / BM)), block(kThreads);
     if (fmt == kMX)
         hipLaunchKernelGGL(gemm_w4a4_kernel<kMX>, grid, block, 0, stream, M, N, K, a_codes, a_scales,

@@ -72,3 +72,25 @@ W16_DECODE, W16_SPLIT = -2, -1
     (5, 40832, 512, W16_SPLIT), (1, 47216, 640, W16_SPLIT), (3, 47888, 768, W16_SPLIT), (7, 28608, 640, W16_SPLIT)])
 def test_w4a16_decode_kernel(rules, M, N, K, kernel):
     assert rules.w4a16_(M, N, K, K) == kernel
+
+
+@pytest.mark.parametrize("N", [1 << 27, 3 << 27, (1 << 31) - 16])
+def test_no_launch_of_2_to_the_32_threads(rules, N):
+    """Weight matrices with so many rows that a workgroup per tile would need a grid of 2^32
+    threads or more stay with the kernels that ran them before the tiles."""
+    tiles = lambda M, tm, tn: -(-M // tm) * -(-N // tn)
+    limit = (1 << 32) // 512
+    for M in (1, 4, 16):
+        assert rules.w4a16_(M, N, 128, 128) == W16_SPLIT or -(-N // 16) < limit
+    for M in (33, 64, 65, 150, 1000):
+        t = rules.w4a16_(M, N, 128, 128)
+        assert t == W16_SPLIT or tiles(M, *((64, 64), (64, 128), (128, 128), (128, 128))[t]) < limit
+    for fmt in (NV, MX):
+        for M in (17, 40, 64):
+            t = rules.decode_(fmt, M, N, 128)
+            assert t == SKINNY or tiles(M, 64, {T32x32: 32, T32x128: 128, T64x32: 32, T64x64F: 64}[t]) < limit
+        for M in (65, 130, 150, 1000):
+            for big in (0, 1):
+                t = rules.product_(fmt, M, N, 128, big)
+                assert t in (-1, 5) or tiles(M, *((64, 64), (64, 128), (128, 128), (64, 128), (128, 128))[t]) < limit
+                assert t != 5 or big

@@ -94,3 +94,36 @@ def test_no_launch_of_2_to_the_32_threads(rules, N):
                 t = rules.product_(fmt, M, N, 128, big)
                 assert t in (-1, 5) or tiles(M, *((64, 64), (64, 128), (128, 128), (64, 128), (128, 128))[t]) < limit
                 assert t != 5 or big
+
+
+PRODUCT = ["64x64", "64x128", "128x128", "64x128 deep", "128x128 deep", "256x256"]
+DECODE = {-1: "skinny", 5: "32x32", 6: "32x128", 7: "64x32", 8: "64x64 few"}
+W4A16 = ["64x64", "64x128", "128x128", "128x128x8"]
+
+
+def test_shapes_of_the_gpu_tests_reach_their_kernels(rules):
+    """The kernel that each GPU test names for a shape is the one the rules pick for it."""
+    from tests import (test_gpu_decode_tiles, test_gpu_gemm_multiround_tiles, test_gpu_gemm_tiles, test_gpu_graph,
+                       test_gpu_product_instances, test_gpu_w4a16_decode, test_gpu_w4a16_tiles)
+
+    def w4a4(fmt, M, N, K):
+        if M <= 64:
+            return DECODE[rules.decode_(fmt, M, N, K)]
+        return PRODUCT[rules.product_(fmt, M, N, K, K % (256 if fmt == NV else 128) == 0)]
+
+    def w4a16(M, N, K):
+        t = rules.w4a16_(M, N, K, K)
+        return W4A16[t] if t >= 0 else "decode" if t == W16_DECODE else "split" if rules.w4a16_splits_(M, N, K) > 1 else "unsplit"
+
+    wrong = [(name, f, M, N, K, w4a4(f, M, N, K))
+             for module in (test_gpu_decode_tiles.CASES, test_gpu_gemm_tiles.CASES, test_gpu_gemm_multiround_tiles.CASES,
+                            test_gpu_product_instances.W4A4)
+             for name, fmts, M, N, K in module for f in fmts if w4a4(f, M, N, K) != name]
+    p = test_gpu_product_instances
+    wrong += [(name, M, N, K, w4a16(M, N, K))
+              for name, M, N, K in p.W4A16 + p.W4A16_STRIDED + p.W4A16_SPECIAL + test_gpu_graph.W4A16 +
+              [("64x64", *shape) for shape in test_gpu_w4a16_tiles.SMALL] +
+              [case[:4] for case in test_gpu_w4a16_tiles.LARGE] +
+              [("decode", M, *shape) for M in test_gpu_w4a16_decode.ROWS for shape in test_gpu_w4a16_decode.SHAPES]
+              if w4a16(M, N, K) != name]
+    assert not wrong

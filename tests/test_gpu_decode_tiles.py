@@ -10,25 +10,26 @@ from tests.test_gpu_parity import MX, NV, log, run_gemm_case
 
 pytestmark = pytest.mark.gpu
 
-# the dispatch's costs pick the named tile for both formats
+# (tile, formats, M, N, K): the dispatch picks the named tile (asserted by the CPU test of its rules)
 CASES = [
-    (17, 4113, 2176),       # 32 x 32: five stages of 512, the last a quarter full
-    (32, 4200, 2944),
-    (31, 32000, 640),       # 32 x 128: three stages of 256, ring of three
-    (64, 4113, 640),        # 64 x 32: two stages
-    (33, 4100, 2432),
-    (50, 8300, 640),        # 64 x 64 with K shared by four sets of waves
-    (64, 8225, 2176),
+    ("skinny", (NV, MX), 17, 4113, 2176),
+    ("32x32", (NV, MX), 32, 4200, 2944),        # six stages of 512, the last three quarters full
+    ("32x128", (NV, MX), 31, 32000, 640),       # three stages of 256, ring of three
+    ("64x32", (NV,), 64, 4113, 640),            # two stages
+    ("64x64 few", (MX,), 64, 4113, 640),        # K shared by four sets of waves
+    ("skinny", (NV,), 33, 4100, 2432),
+    ("64x32", (MX,), 33, 4100, 2432),
+    ("64x64 few", (NV, MX), 50, 8300, 640),
+    ("64x64 few", (NV, MX), 64, 8225, 2176),
 ]
 
 
-@pytest.mark.parametrize("fmt", [NV, MX])
-@pytest.mark.parametrize("M,N,K", CASES)
+@pytest.mark.parametrize("fmt,M,N,K", [(f, M, N, K) for _, fmts, M, N, K in CASES for f in fmts])
 def test_decode_tiles(fmt, M, N, K):
     log("decode tiles fmt=%d M=%d N=%d K=%d" % (fmt, M, N, K))
     run_gemm_case(fmt, M, N, K, seed=M + N + K, dist="student_t", all_points=False)
 
 
 def test_one_short_stage():
-    """64 x 32 tiles with K = 128: one stage, a quarter full, half a unit of the image."""
+    """K = 128: one stage, half full, half a unit of the image."""
     run_gemm_case(MX, 64, 4200, 128, seed=9, dist="student_t", all_points=False)

@@ -14,24 +14,25 @@ from tests.test_gpu_parity import MX, NV, DEV, _rand, log, run_gemm_case
 
 pytestmark = pytest.mark.gpu
 
-# (formats, M, N, K): the dispatch's costs pick the named tile
+# (tile, formats, M, N, K): the dispatch picks the named tile (asserted by the CPU test of its rules)
 CASES = [
-    ((NV, MX), 65, 66, 128),        # 64 x 64: one stage, half a scale group
-    ((NV, MX), 127, 65, 640),
-    ((NV, MX), 129, 130, 2176),     # 64 x 64: five stages, K ends a quarter into the last
-    ((NV, MX), 193, 300, 4096),     # 64 x 64: eight whole stages
-    ((NV,), 130, 12000, 384),       # 64 x 128
-    ((MX,), 320, 6500, 384),
-    ((NV,), 129, 10100, 2176),      # 64 x 128: nine stages of 256
-    ((MX,), 257, 8200, 640),        # 128 x 128
-    ((MX,), 257, 8200, 1920),
-    ((NV,), 256, 32700, 128),
-    ((NV,), 1030, 16500, 1152),
-    ((NV, MX), 8100, 4000, 512),    # 256 x 256, two tiles per workgroup
+    ("64x128", (NV,), 65, 66, 128),             # half a stage
+    ("64x128 deep", (MX,), 65, 66, 128),
+    ("64x64", (NV, MX), 127, 65, 640),
+    ("64x64", (NV, MX), 129, 130, 2176),        # five stages, K ends a quarter into the last
+    ("64x64", (NV, MX), 193, 300, 4096),        # eight whole stages
+    ("64x128", (NV,), 130, 12000, 384),
+    ("64x128 deep", (MX,), 320, 6500, 384),
+    ("64x128 deep", (NV,), 129, 10100, 2176),   # nine stages of 256
+    ("128x128 deep", (MX,), 257, 8200, 640),
+    ("128x128 deep", (MX,), 257, 8200, 1920),
+    ("128x128", (NV,), 256, 32700, 128),
+    ("64x128", (NV,), 1030, 16500, 1152),
+    ("256x256", (NV, MX), 8100, 4000, 512),     # two tiles per workgroup
 ]
 
 
-@pytest.mark.parametrize("fmt,M,N,K", [(f, M, N, K) for fmts, M, N, K in CASES for f in fmts])
+@pytest.mark.parametrize("fmt,M,N,K", [(f, M, N, K) for _, fmts, M, N, K in CASES for f in fmts])
 def test_tile_kernels(fmt, M, N, K):
     log("gemm tiles fmt=%d M=%d N=%d K=%d" % (fmt, M, N, K))
     run_gemm_case(fmt, M, N, K, seed=M + N + K, dist="student_t", all_points=M * N <= 60000)

@@ -178,11 +178,16 @@ def test_kv4_graph_replays_match_eager():
     log("kv4 graph replays match")
 
 
-@pytest.mark.parametrize("M,N,K", [(16, 640, 4096), (5, 1536, 1024)])
+# kernel, M, N, K: the dispatch's pick (asserted by the CPU test of its rules)
+W4A16 = [("decode", 16, 640, 4096), ("decode", 5, 1536, 1024), ("split", 16, 640, 16256), ("unsplit", 9, 16400, 256),
+         ("64x64", 65, 640, 1024)]
+
+
+@pytest.mark.parametrize("M,N,K", [shape for _, *shape in W4A16])
 def test_w4a16_graph_replays_match_eager(M, N, K):
-    """W4A16 product (row-major and packed weights) captured and replayed.
-    640 rows give 10 workgroups, so K is split and the FP32 partial sums meet
-    in the workspace through the reduction kernel; 1536 rows are not split."""
+    """W4A16 product (row-major and packed weights) captured and replayed: the
+    decode kernel, K split over workgroups (the FP32 partial sums meet in the
+    workspace through the reduction kernel), one pass of the same kernel, a tile."""
     log(f"graph w4a16 M={M} N={N} K={K}")
     gen = torch.Generator().manual_seed(5 + M)
     w = (torch.randn(N, K, generator=gen) * 0.02).to(torch.bfloat16).to(DEV)
@@ -191,7 +196,7 @@ def test_w4a16_graph_replays_match_eager(M, N, K):
     x1 = (torch.randn(M, K, generator=gen) * 2.0).to(torch.bfloat16).to(DEV)
     x2 = (torch.randn(M, K, generator=gen) * 2.0).to(torch.bfloat16).to(DEV)
     nws = max(reqat.reqat_w4a16_workspace_bytes(M, N, K), 16)
-    if N == 640:
+    if ("split", M, N, K) in W4A16:
         assert reqat.reqat_w4a16_workspace_bytes(M, N, K) > 0, "expected a split product"
 
     def bufs():

@@ -737,7 +737,7 @@ def run_gemm_case(fmt, M, N, K, seed, dist="normal", wstd=0.02, g=(None, None), 
                                    (20, 150, 640), (32, 96, 384)])
 def test_gemm_parity(fmt, M, N, K):
     """(100, 96, 384), (200, 130, 1152) and (65, 300, 128): K % 256 == 128 with
-    M > 64, which NVFP4 runs on the 128 x 128 register-staged kernel.
+    M > 64, which NVFP4 cannot run on the 256 x 256 tiles.
     (20, 150, 640) and (32, 96, 384): two 16-row activation tiles in the
     decode-shaped product, row-major and packed, with a ragged N and half a
     256-element chunk at the end of K."""
@@ -1012,8 +1012,8 @@ def test_products_into_strided_output(fmt, M, N, K):
     """Products written into a wider row-major buffer (ldy > N, e.g. one slice
     of a fused QKV output) and, for the linear layer, read from a wider
     activation buffer (ldx > K): the slice matches the oracle and the padding
-    columns keep their poison.  Covers the skinny (M <= 64), tiled and
-    register-staged (NVFP4 with K % 256 == 128) kernels."""
+    columns keep their poison.  Covers the skinny kernel and tiles, with K
+    whole stages and not (K % 256 == 128)."""
     log("strided products fmt=%d M=%d N=%d K=%d" % (fmt, M, N, K))
     seed = 3 * M + N + K
     xa = _rand(M, K, seed, "student_t", outliers=max(1, K // 100))

@@ -9,8 +9,11 @@ from tests.test_gpu_parity import _rand, _w4a16_weights, log, run_w4a16
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("M", [1, 3, 4, 5, 8, 9, 13, 16])
-@pytest.mark.parametrize("N,K", [(17, 128), (100, 896), (33, 1152), (48, 4736)])
+ROWS, SHAPES = [1, 3, 4, 5, 8, 9, 13, 16], [(17, 128), (100, 896), (33, 1152), (48, 4736)]
+
+
+@pytest.mark.parametrize("M", ROWS)
+@pytest.mark.parametrize("N,K", SHAPES)
 def test_decode_rows(M, N, K):
     log("w4a16 decode M=%d N=%d K=%d" % (M, N, K))
     run_w4a16(_rand(M, K, M + N, "student_t", outliers=max(1, K // 100)), *_w4a16_weights(N, K, M + N))

@@ -15,8 +15,11 @@ from tests.test_gpu_parity import DEV, GEMM_TOL, _rand, _w4a16_weights, log, run
 pytestmark = pytest.mark.gpu
 
 
-# (M, N, K): the dispatch's costs pick 64 x 64 tiles (stages of 128)
-@pytest.mark.parametrize("M,N,K", [(65, 33, 128), (129, 130, 256), (200, 65, 384), (130, 100, 640), (65, 1, 1152)])
+# 64 x 64 tiles (stages of 128); the dispatch's picks are asserted by the CPU test of its rules
+SMALL = [(65, 33, 128), (129, 130, 256), (200, 65, 384), (130, 100, 640), (65, 1, 1152)]
+
+
+@pytest.mark.parametrize("M,N,K", SMALL)
 def test_small_tiles(M, N, K):
     log("w4a16 tiles M=%d N=%d K=%d" % (M, N, K))
     run_w4a16(_rand(M, K, M + N, "student_t", outliers=max(1, K // 100)), *_w4a16_weights(N, K, M + N))
@@ -41,10 +44,13 @@ def _dequantized(wc, ws):
     return (v.reshape(len(ws), -1, 32) * e[:, :, None]).reshape(len(ws), -1)
 
 
-# tile by the costs                         64 x 128               128 x 128               128 x 128, eight waves
-@pytest.mark.parametrize("M,N,K,out", [(65, 12000, 384, "f32"), (100, 17003, 1152, "bf16"),
-                                       (300, 27700, 256, "f32"), (700, 10001, 1280, "bf16"),
-                                       (385, 5105, 1152, "bf16"), (200, 16001, 640, "f32")])
+LARGE = [("64x128", 65, 12000, 384, "f32"), ("64x128", 100, 17003, 1152, "bf16"), ("64x128", 300, 27700, 256, "f32"),
+         ("64x128", 385, 5105, 1152, "bf16"), ("64x128", 65, 8225, 128, "f32"),
+         ("128x128", 700, 10001, 1280, "bf16"), ("128x128", 641, 9001, 768, "f32"),
+         ("128x128x8", 200, 16001, 640, "f32"), ("128x128x8", 770, 4113, 896, "bf16"), ("128x128x8", 770, 4113, 1024, "f32")]
+
+
+@pytest.mark.parametrize("M,N,K,out", [case for _, *case in LARGE])
 def test_large_tiles(M, N, K, out):
     log("w4a16 large tiles M=%d N=%d K=%d" % (M, N, K))
     g = torch.Generator(device=DEV).manual_seed(M + N)

@@ -437,20 +437,27 @@ __global__ __launch_bounds__(kThreads) void kv4_quantize_kernel(
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // a wave step: kKvU adjacent segments of 64 blocks, one block per lane each
-    for (int64_t base = ((int64_t)blockIdx.x * 4 + wave) * (64 * kKvU); base < total;
-         base += (int64_t)gridDim.x * 4 * 64 * kKvU) {
-        float d[kKvU][16];
+    auto walk = [&](auto snap) {
+        for (int64_t base = ((int64_t)blockIdx.x * 4 + wave) * (64 * kKvU); base < total;
+             base += (int64_t)gridDim.x * 4 * 64 * kKvU) {
+            float d[kKvU][16];
 #pragma unroll
-        for (int u = 0; u < kKvU; ++u) {
-            const int64_t blk = base + 64 * u + lane;
-            kv4_load<SRC>(x, shift, lds_shift, blk < total ? blk : total - 1, nb, ldx, narrow, d[u]);
-        }
+            for (int u = 0; u < kKvU; ++u) {
+                const int64_t blk = base + 64 * u + lane;
+                kv4_load<SRC>(x, shift, lds_shift, blk < total ? blk : total - 1, nb, ldx, narrow, d[u]);
+            }
 #pragma unroll
-        for (int u = 0; u < kKvU; ++u) {
-            const int64_t blk = base + 64 * u + lane;
-            if (blk < total) kv4_emit<OUT, SRC == kNoShift>(d[u], kv4_block_max(d[u]), blk, nb, narrow, G, codes, scales, y, ldy);
+            for (int u = 0; u < kKvU; ++u) {
+                const int64_t blk = base + 64 * u + lane;
+                if (blk < total)
+                    kv4_emit<OUT, decltype(snap)::value>(d[u], kv4_block_max(d[u]), blk, nb, narrow, G, codes, scales, y,
+                                                         ldy);
+            }
         }
-    }
+    };
+    // under a g that is not a power of two every block takes the exact path, and the snap would be wasted
+    if (SRC == kNoShift && G.f32) walk(std::integral_constant<bool, SRC == kNoShift>{});
+    else walk(std::false_type{});
 }
 
 // Largest (kMax) or smallest v over the 64 lanes of a wave (all active), as a

@@ -311,6 +311,15 @@ def test_kv4_parity_random(shape, shifted):
     assert_kv4_parity(xb, shift, g=2.0 ** -6)
 
 
+@pytest.mark.parametrize("g", [2.0 ** -6, 0.0123456789, 2.0 ** 100, 1.1 * 2.0 ** 100])
+def test_kv4_every_pattern_unshifted_under_a_given_scale(g):
+    """Without a shift a power-of-two g takes the snap, any other the threshold path."""
+    log("kv4 exhaustive bf16 patterns unshifted, given g=%r" % g)
+    pats = np.random.default_rng(17).permutation(np.arange(65536, dtype=np.uint16)).reshape(64, 1024)
+    assert_kv4_parity(pats, None, g=float(np.float32(g)))
+    assert_kv4_parity(np.sort(pats.reshape(-1)).reshape(64, 1024)[:, :1008], None, g=float(np.float32(g)))
+
+
 def test_kv4_exhaustive_patterns_and_specials():
     log("kv4 exhaustive bf16 patterns with a shift, specials, strided rows")
     pats = np.random.default_rng(13).permutation(np.arange(65536, dtype=np.uint16)).reshape(64, 1024)

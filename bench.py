@@ -30,11 +30,13 @@ if ROOT not in sys.path:
 
 METRIC = "W4A4 GEMM TFLOPS & % FP4 MFMA peak (prefill); quantize/decode HBM GB/s"
 GEMM_SOURCES = ["paper_2606_15682_amd/csrc/gemm_tile256.hip", "paper_2606_15682_amd/csrc/gemm.hip",
+                "paper_2606_15682_amd/csrc/dispatch.h", "paper_2606_15682_amd/csrc/g2l.h",
                 "paper_2606_15682_amd/csrc/fp4_device.h"]
 # the sources a committed traffic summary was measured on, per kind of row
 TRAFFIC_SOURCES = {
     "gemm": GEMM_SOURCES,
-    "w4a16": ["paper_2606_15682_amd/csrc/gemm_w4a16.hip", "paper_2606_15682_amd/csrc/fp4_device.h"],
+    "w4a16": ["paper_2606_15682_amd/csrc/gemm_w4a16.hip", "paper_2606_15682_amd/csrc/dispatch.h",
+              "paper_2606_15682_amd/csrc/g2l.h", "paper_2606_15682_amd/csrc/fp4_device.h"],
     "kv4": ["paper_2606_15682_amd/csrc/kv4.hip", "paper_2606_15682_amd/csrc/fp4_device.h"],
     "skinny": ["paper_2606_15682_amd/csrc/gemm_skinny.hip", "paper_2606_15682_amd/csrc/fp4_device.h"],
     "sem": ["paper_2606_15682_amd/csrc/sem.hip"],

@@ -201,11 +201,14 @@ reqat_status reqat_fakequant_mxfp4_rht(const void *x, int64_t rows, int64_t cols
  *   y [M][ldy] of y_dtype, ldy >= N.
  *   workspace: device scratch of reqat_w4a16_workspace_bytes(M, N, K) bytes
  *              (4-byte aligned; may be NULL when that is 0): FP32 partial sums
- *              when K is split over several workgroups (few weight rows).
+ *              when K is split over several workgroups (few weight rows).  The
+ *              size holds for every kernel that may run the product; those
+ *              that keep K in a workgroup leave the scratch untouched.
  * Requirements: K % 128 == 0.  M == 0 or N == 0 is a no-op; K == 0 writes zeros.
- * Designed for decode (small M): one pass over the weights.  The result is
- * deterministic: the split is a function of (M, N, K) alone and the partial
- * sums are added in a fixed order.
+ * Up to 32 rows of x one pass over the weights; beyond, tiles of up to 128
+ * rows of x where they are faster.  The result is deterministic: the kernel
+ * and the split are functions of the sizes alone (beyond 2^23, of ldx too) and
+ * the partial sums are added in a fixed order.
  */
 reqat_status reqat_gemm_w4a16(int64_t M, int64_t N, int64_t K, const void *x, int64_t ldx,
                               const uint8_t *w_codes, const uint8_t *w_scales, void *y, reqat_dtype y_dtype,

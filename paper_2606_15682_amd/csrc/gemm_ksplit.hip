@@ -25,8 +25,10 @@
 //
 // What bounds each tile: NVFP4 the matrix cores and the decode beside them
 // (64 x 64: 2.1 us per 1000 elements of K with one tile per CU, 0.93 us would be
-// the MFMAs alone), MXFP4 the load path (64 x 64: 1.3 us; 128 x 128: 4 us, 5 for two
-// tiles per CU).  Measured against the 256 x 256 kernel, one graph, weights
+// the MFMAs alone; counters: matrix pipe busy on 0.34 of the cycles, VALU issue on 0.49).
+// MXFP4 (64 x 64: 1.3 us; 128 x 128: 4 us, 5 for two tiles per CU): issue and waits,
+// with the matrix pipe busy on 0.05 (64 x 32, 40 to 50 scalar instructions per MFMA) to 0.25 of the
+// cycles (128 x 128, 5 of them) and waves waiting for a counter or barrier on 0.36 to 0.52 of theirs.  Measured against the 256 x 256 kernel, one graph, weights
 // from HBM: NVFP4 256 x 3584 x 18944 331 -> 45 us, 256 x 4608 x 3584 69 -> 19 us;
 // MXFP4 777 x 6912 x 5120 37 -> 27 us, 777 x 1792 x 5120 36 -> 17 us; NVFP4
 // 777 x 5120 x 3456 (K % 256 = 128, where the general kernel ran) 437 -> 43 us.

@@ -10,8 +10,9 @@
 // tiles of 32 x 32 (v_mfma_f32_32x32x16_bf16); where WK = 2, two sets of waves share out K
 // and their partial sums meet in LDS at the end, added in a fixed order.  Weights are
 // decoded in registers a step ahead of their MFMAs (four conversions per fragment, which
-// apply the block's scale).  512 x 27648 x 5120: 130 us, 1.1 PFLOP/s, MFMAs on 74% of the
-// cycles at the clock the card holds (a large library product in bfloat16: 1.39); more
+// apply the block's scale).  512 x 27648 x 5120: 130 us, 1.1 PFLOP/s (a large library product in
+// bfloat16: 1.39); the matrix pipe busy on 0.60 of the cycles, waves waiting to issue on 0.39 of theirs
+// (4.5 VALU per MFMA); 160 tiles on 256 CUs (512 x 5120 x 13824): 0.40 of the cycles.  More
 // buffers, up to the whole LDS, gave at most 10% for single rounds and cost 20% elsewhere.
 //
 // In a 64-element slice of K, lane (r, h) takes the 32 elements of half h of row r: one MX

@@ -328,7 +328,7 @@ __device__ __forceinline__ uint32_t kv4_pack8(const float *c) {
 // rounded to a multiple of 2^-12 (by adding 3072: the sum lies in [2048, 4096)),
 // which gives a half-integer exactly where d / H is one and keeps the side
 // elsewhere; then rint decides as above, ties included, and no block is left
-// undecided.  Values of a 32768 x 1024 cache slice: 40 -> 28 us.
+// undecided.  The pass over values of a 32768 x 1024 cache slice: 40 -> 26 us.
 template <int OUT, bool kBf16>
 __device__ __forceinline__ uint32_t kv4_emit(const float (&d)[16], uint32_t am, int64_t blk, int64_t nb, bool narrow,
                                              const Kv4G &G, uint8_t *__restrict__ codes, uint8_t *__restrict__ scales,

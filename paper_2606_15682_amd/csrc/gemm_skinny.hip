@@ -1,5 +1,5 @@
 // Skinny W4A4 GEMM for gfx950 (M <= 64: decode-shaped products; from 17 rows on
-// only where the weight matrix is short, see gemm.hip).
+// only where the rules of dispatch.h expect no less time of a tile).
 //
 // Y[M][N] = g_a g_b * sum_k A^[m][k] B^[n][k] with few activation rows: the
 // weights B dominate the traffic and must stream from memory once, spread
